@@ -384,8 +384,7 @@ size_t slab_bytes(const BlockPlan& P, int64_t tokens, bool bwd, int nlin = 4) {
             const atp_shard& g = P.g[L];
             if ((bwd ? g.bwd_size : g.red_size) <= 1) continue;
             const int64_t N = bwd ? g.k_loc : g.n_loc, K = bwd ? g.n_loc : g.k_loc;
-            int64_t ks = 0;
-            const int S = atp::nt_split_plan(mc, N, K, &ks);
+            const int S = atp::nt_split_limit(mc, N, K);
             if (S > 1) most = std::max(most, (size_t)S * mc * N * 4);
         }
     }
@@ -394,27 +393,38 @@ size_t slab_bytes(const BlockPlan& P, int64_t tokens, bool bwd, int nlin = 4) {
 
 bool valid_layout(int32_t l) { return l == ATP_W_KN || l == ATP_W_NK; }
 
-// True when the forward of linear L with `chunks` chunks reads weights
-// stored [k][n] as they are on the workspace path: its products stream NN
-// as fast as NT from a W^T copy and are not split over k.  A linear whose
-// group has one member runs one product over all tokens; the others run one
-// product per chunk.  Otherwise the forward first copies W^T into the
-// workspace.
-bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks) {
+// True when the workspace holds a place for W^T of linear L (weights stored
+// [k][n]): at some chunk count the linear's products may split over k or do
+// not fill 256 x 256 tiles.  The place is there whatever the chunk count, as
+// the slabs'.  A linear whose group has one member runs one product over all
+// tokens; the others run one product per chunk.
+bool fwd_may_copy_w(const BlockPlan& P, int L, int64_t tokens) {
     const atp_shard& g = P.g[L];
-    if (g.red_size <= 1) return atp::nn_streams_like_nt(tokens, g.n_loc);
-    const int64_t mc = tokens / chunks;
-    int64_t ks = 0;
-    return atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) <= 1 &&
-           atp::nn_streams_like_nt(mc, g.n_loc);
+    for (int c = 1; c <= ATP_MAX_CHUNKS; ++c) {
+        if (tokens % c) continue;
+        const int64_t mc = tokens / c;
+        if (g.red_size <= 1 ? !atp::nn_large_tiles(tokens, g.n_loc)
+                            : atp::nt_split_limit(mc, g.n_loc, g.k_loc) > 1 ||
+                                  !atp::nn_large_tiles(mc, g.n_loc))
+            return true;
+    }
+    return false;
 }
 
-// True when some chunk count makes the forward of linear L copy W^T (the
-// workspace holds its copy whatever the chunk count, as for the slabs).
-bool fwd_may_copy_w(const BlockPlan& P, int L, int64_t tokens) {
-    for (int c = 1; c <= ATP_MAX_CHUNKS; ++c)
-        if (tokens % c == 0 && !fwd_reads_w(P, L, tokens, c)) return true;
-    return false;
+// True when the forward of linear L with `chunks` chunks reads weights
+// stored [k][n] as they are on the workspace path: there is no place for a
+// copy, or its products are not split over k and would not gain from W^T what
+// copying it costs (4 us and its bytes read and written at 3.5 TB/s).  Split
+// products run from W^T.
+bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks) {
+    if (!fwd_may_copy_w(P, L, tokens)) return true;
+    const atp_shard& g = P.g[L];
+    const bool one = g.red_size <= 1;
+    const int64_t m = one ? tokens : tokens / chunks;
+    int64_t ks = 0;
+    if (!one && atp::nt_split_plan(m, g.n_loc, g.k_loc, &ks) > 1) return false;
+    const double copy = 4.0 + 4.0 * (double)g.k_loc * (double)g.n_loc / 3.5e6;
+    return (one ? 1 : chunks) * atp::nn_extra_us(m, g.n_loc, g.k_loc) < copy;
 }
 
 // The forward's pieces: the slabs, and W^T ([n_loc][k_loc]) of weights

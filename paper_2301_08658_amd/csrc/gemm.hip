@@ -1,12 +1,13 @@
 // bf16 x bf16 -> fp32 MFMA GEMMs for gfx950 (CDNA4) with fused epilogues.
 //
-// One kernel, gemm_nt_kernel, serves the three products of a shard linear
+// gemm_nt_kernel (tiles of 256 rows) and gemm_small_kernel (smaller tiles)
+// serve the three products of a shard linear
 // (Sec. 3.2 forward Y = X W; Sec. 4.2 backward dX = dY W^T, dW = X^T dY) in
 // each operand layout: an operand is either contiguous along k (X, dY, and
 // W in dX; the transposed copies W^T, X^T, dY^T of the workspace path) or
 // contiguous along its rows (W in the forward, X and dY in dW without a
-// workspace).  The kernel is described below; every layout sums an output
-// element's products in the same order, so the layouts give the same bits.
+// workspace).  The kernels are described below; every layout and tile sums an
+// output element's products in the same order, so they give the same bits.
 //
 //   * Operands go global -> LDS with buffer_load_dwordx4 ... lds (no
 //     register staging).  A buffer resource per operand gives zero fill for
@@ -334,17 +335,20 @@ __device__ __forceinline__ bf16x8 frag(const uint16_t* src, int r0, int ks, int 
 template <int ROWS>
 __device__ __forceinline__ int tpos(int k, int c) {
     if constexpr (ROWS == 160) return (c + 2 * ((k >> 3) & 1)) % 20;   // rotation by 0 / 2
-    else return c ^ (2 * (k & 3) + 8 * ((k >> 3) & 1));                // XOR, 32 chunks
+    else if constexpr (ROWS == 64)   // two k rows per 256 bytes
+        return c ^ (2 * ((k >> 1) & 1) + 4 * ((k >> 3) & 1));
+    else return c ^ (2 * (k & 3) + 8 * ((k >> 3) & 1));                // XOR, 16 or 32 chunks
 }
 template <int ROWS>
 __device__ __forceinline__ int tchunk(int k, int pos) {   // inverse of tpos
     if constexpr (ROWS == 160) return (pos + 20 - 2 * ((k >> 3) & 1)) % 20;
-    else return pos ^ (2 * (k & 3) + 8 * ((k >> 3) & 1));
+    else return tpos<ROWS>(k, pos);
 }
 
 template <int ROWS, int NI = NW>
 struct CopyT {
-    static_assert(ROWS == 160 || ROWS == 256, "tile widths with a conflict-free layout");
+    static_assert(ROWS == 64 || ROWS == 128 || ROWS == 160 || ROWS == 256,
+                  "tile widths with a conflict-free layout");
     static constexpr int CPK = ROWS / 8;            // 16-byte chunks per k row
     static constexpr int WI = BK * CPK / 64;        // copy instructions per stage
     static constexpr int PER = (WI + NI - 1) / NI;  // per issuing wave (some one fewer)
@@ -640,6 +644,169 @@ __global__ __launch_bounds__(nt::NT, 1) void gemm_nt_kernel(KArgs a) {
     }
 }
 
+// ---------------------------------------------------------------------------
+// Smaller tiles (256 x 128, 128 x 128, 64 x 128, 64 x 64), for products whose
+// large tiles would leave CUs idle or end in a nearly empty round.
+//
+//   * The waves have two roles.  Four producer waves, one per SIMD, only issue
+//     the copies into an LDS ring of S stages and wait for them; the consumer
+//     waves read fragments and multiply.  A copy instruction holds up the wave
+//     that issues it while the CU's memory path is busy, and in a wave that
+//     also multiplies the matrix core idles behind it (one role for all waves:
+//     1024 x 1024 x 4096 on 64 tiles of 128 x 128 took 40 us, with two roles
+//     28; 1024 x 6144 x 8192 108 and 103; the 256 x 160 tiles take 69 and 134).
+//   * One workgroup barrier per K step: at barrier p step p has landed and
+//     every consumer has read step p - 1, whose slot the producers refill.
+//   * A consumer reads the second k-slice's fragments under the first one's
+//     MFMAs, and the next step's first slice under the second's.
+//   * What bounds them is the copy path: a CU streams about 25-40 B/clk
+//     whatever the tile, so a tile's K step costs its (rows + columns) * 128
+//     bytes over that, and smaller tiles pay only where the large ones leave
+//     CUs without one.
+// Copies, LDS layouts, fragments and the order of an element's products are
+// those of the large tiles, so every configuration gives the same bits.
+// ---------------------------------------------------------------------------
+namespace st {
+
+// BM x BN tile, WGM x WGN consumer waves, STAGES LDS stages of K step 64,
+// PERCU workgroups per CU (registers and LDS allow them)
+template <int BM_, int BN_, int WGM_, int WGN_, int STAGES_, int PERCU_>
+struct Cfg {
+    static constexpr int PW = 4;        // producer waves
+    static constexpr int GROUP = 4;     // row tiles swept together
+    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, STAGES = STAGES_,
+                         PERCU = PERCU_;
+    static constexpr int NW = WGM * WGN, NT = (NW + PW) * 64, BK = 64;
+    static constexpr int WM = BM / WGM, WN = BN / WGN, FM = WM / 16, FN = WN / 16;
+    static constexpr int A_EL = BM * BK, STAGE = (BM + BN) * BK, LDS_EL = STAGES * STAGE;
+    static_assert(FM * 16 == WM && FN * 16 == WN, "wave tile of whole MFMA tiles");
+    static_assert(LDS_EL * 2 * PERCU <= 160 * 1024, "LDS of one CU");
+    static constexpr int MINW = ((NW + PW) * PERCU + 3) / 4;   // waves per SIMD
+};
+
+// One workgroup per CU with a deep ring (two for 64 x 64).  Two 64 x 128
+// workgroups per CU with three stages each were slower (2048 x 1024 x 8192,
+// operand A from HBM: 57 us against 49), deeper rings and three 64 x 64
+// workgroups per CU no faster, two producer waves instead of four 20-60%
+// slower.
+using Tile256x128 = Cfg<256, 128, 4, 2, 3, 1>;   // 144 KB, waves of 64 x 64
+using Tile128 = Cfg<128, 128, 2, 4, 4, 1>;       // 128 KB, waves of 64 x 32
+using Tile64x128 = Cfg<64, 128, 2, 2, 4, 1>;     // 96 KB, waves of 32 x 64
+using Tile64 = Cfg<64, 64, 2, 2, 4, 2>;          // 64 KB, waves of 32 x 32
+
+}  // namespace st
+
+template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16>
+__global__ __launch_bounds__(C::NT, C::MINW) void gemm_small_kernel(KArgs a) {
+    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NW = C::NW, S = C::STAGES, PW = C::PW;
+    constexpr int FM = C::FM, FN = C::FN;
+    using CA = nt::OpCopy<BM, A_K, BK, PW>;
+    using CB = nt::OpCopy<BN, B_K, BK, PW>;
+    static_assert(CA::PER * PW == CA::WI && CB::PER * PW == CB::WI, "equal shares");
+    constexpr int L = CA::PER + CB::PER;   // copy instructions per producer wave and step
+    __shared__ __attribute__((aligned(1024))) uint16_t smem[C::LDS_EL];
+    __builtin_amdgcn_s_setprio(1);   // above the reductions sharing the CU, as the large tiles'
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave / C::WGN, wn = wave % C::WGN;
+    const int ntiles = a.tiles_m * a.tiles_n;
+    const int logical = xcd_logical();
+    const int split = logical / ntiles;
+    int tm, tn;
+    group_coords<C::GROUP>(logical - split * ntiles, a.tiles_m, a.tiles_n, tm, tn);
+    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+    const int64_t kb = (int64_t)split * a.ksplit;
+    const int64_t kn = min(a.K - kb, a.ksplit);
+
+    const int nk = (int)((kn + BK - 1) / BK);
+    auto slot = [&](int q) { return smem + (q % S) * C::STAGE; };
+    if (wave >= NW) {
+        const int pw = wave - NW;
+        CA ca;
+        CB cb;
+        ca.init(a.A + (A_K ? kb : kb * a.lda), a.lda, m0, a.M, kn, pw, lane);
+        cb.init(a.B + (B_K ? kb : kb * a.ldb), a.ldb, n0, a.N, kn, pw, lane);
+        auto issue = [&](int q) {
+            ca.issue(slot(q), (int64_t)q * BK, pw);
+            cb.issue(slot(q) + C::A_EL, (int64_t)q * BK, pw);
+        };
+        // wait until this wave's copies have landed except the newest `fly` steps'
+        auto wait_copies = [&](int fly) {
+            static_assert(S >= 3 && S <= 4 && (S - 1) * L < 64, "copies in flight");
+            if (S >= 4 && fly == 3) wait_vmcnt<(S >= 4 ? 3 : 0) * L>();
+            else if (fly == 2) wait_vmcnt<2 * L>();
+            else if (fly == 1) wait_vmcnt<L>();
+            else wait_vmcnt<0>();
+        };
+        for (int q = 0; q < S && q < nk; ++q) issue(q);
+        for (int p = 0; p < nk; ++p) {
+            // step p has landed: issued so far are the steps up to S - 1
+            // (p = 0), else up to p + S - 2
+            wait_copies(min(p == 0 ? S - 1 : S - 2, nk - 1 - p));
+            nt::barrier();   // barrier p: step p visible, slot of step p - 1 read by all
+            if (p > 0 && p - 1 + S < nk) issue(p - 1 + S);
+        }
+        wait_vmcnt<0>();
+        return;
+    }
+    f32x4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 fa[2][FM], fb[2][FN];
+    auto read = [&](int p, int ks) {
+        const uint16_t* sa = slot(p);
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+            fa[ks & 1][i] = nt::op_frag<BM, A_K, BK>(sa, wm * C::WM + i * 16, ks, lane);
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+            fb[ks & 1][j] = nt::op_frag<BN, B_K, BK>(sa + C::A_EL, wn * C::WN + j * 16, ks, lane);
+    };
+    auto mul = [&](int ks) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[ks & 1][j], fa[ks & 1][i],
+                                                                    acc[i][j], 0, 0, 0);
+    };
+    if (nk > 0) {   // (uniform)
+        nt::barrier();   // barrier 0
+        read(0, 0);
+        for (int p = 0; p < nk; ++p) {
+            read(p, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            mul(0);
+            if (p + 1 < nk) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                nt::barrier();   // barrier p + 1
+                read(p + 1, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            mul(1);
+        }
+    }
+
+    // Epilogue: the fragment layout of the large tiles
+    KArgs o = a;
+    if (split) o.C = static_cast<float*>(a.C) + split * a.c_split;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        const int64_t m = m0 + wm * C::WM + i * 16 + (lane & 15);
+        if (m >= a.M) continue;
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int64_t n = n0 + wn * C::WN + j * 16 + 4 * (lane >> 4);
+            if (n >= a.N) continue;
+            float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
+            epilogue_store<EPI, OUT_BF16>(o, m, n, v);
+        }
+    }
+}
+
 KArgs kargs(const GemmProblem& p, int bm, int bn) {
     KArgs a;
     a.A = static_cast<const uint16_t*>(p.A);
@@ -666,68 +833,93 @@ KArgs kargs(const GemmProblem& p, int bm, int bn) {
     return a;
 }
 
-// Products with both operands row-contiguous (TN: dW on the path without a
-// workspace): 256 x 256 tiles (30% fewer copied bytes per FLOP) when their
-// last wave of 256 concurrent tiles is at least 90% full, 256 x 160 otherwise.
-bool fills_waves(const GemmProblem& p, int64_t bn) {
-    constexpr int64_t kCUs = 256;
-    const int64_t tiles = ((p.M + nt::BM - 1) / nt::BM) * ((p.N + bn - 1) / bn);
-    const int64_t waves = (tiles + kCUs - 1) / kCUs;
-    return tiles * 10 >= waves * kCUs * 9;
-}
-
-bool nt_use_256(const GemmProblem& p) { return fills_waves(p, 256); }
-
 // Buffer offsets are 32-bit and a resource covers at most 0x7fffff00 bytes:
 // the rows one tile copies from an operand contiguous along k (BM rows of A,
 // BN rows of B) must span less than that.
 constexpr int64_t kMaxSpan = 0x7fffff00;
 bool rows_fit(int64_t rows, int64_t ld) { return rows * ld * 2 <= kMaxSpan; }
 
-// Tile configuration of an unsplit product with both operands contiguous
-// along k: the one with the least modelled time, (waves of 256 concurrent
-// tiles) x (tile width / relative per-CU rate), where a last wave that is a
-// fraction f full costs 0.5 + 0.5 f of a full one (its tiles share L2 and
-// HBM with fewer others).  Relative rates measured on the block's products
-// with every CU busy: 256 x 160 0.8, 256 x 320 (K steps of 32) 0.9,
-// 256 x 256 with split rings 1.0.  The 256 x 256 tiles are preferred within
-// 5%: they leave CUs to the reductions that run beside a one-wave product.
-enum NtCfg { NT_160, NT_256S, NT_320 };
+// Tile configuration of a product: the one with the least modelled time.  A
+// configuration's tiles run in rounds of 256 * percu; a K step of 64 takes t1
+// us while the CUs hold at most one tile each and few are busy, tf with every
+// CU full (between them linearly in the busy share where a CU holds one tile;
+// two tiles on any one CU make it tf), and a round adds o0 + ox * (tiles / 256)
+// us of prologue and output.  Fitted to launches back to back with operand A
+// from HBM, as in a step (tiles x K steps: us [model]): 256 x 256: 32 x 128 148
+// [152], 256 x 64 103 [109]; 256 x 128: 64 x 128 98 [101], 192 x 128 104 [113], 512 x
+// 64 123 [127]; 128 x 128: 64 x 64 28 [32], 192 x 192 106 [105], 1024 x 64 145 [161];
+// 64 x 128: 256 x 128 49 [50], 128 x 64 22 [24]; 64 x 64: 256 x 64 18 [18],
+// 1024 x 64 64 [62].  A smaller tile has to beat the large ones by 5%: they
+// leave CUs to the reductions that run beside a one-round product.
+enum TileCfg { T_256, T_160, T_320, T_256x128, T_128, T_64x128, T_64, T_COUNT };
 
-double nt_cost(const GemmProblem& p, int64_t bn, double rate) {
+struct TileCost { int bm, bn, percu; double t1, tf, o0, ox; };
+// k-contiguous A (NT, and NN, whose 160-wide tiles are slower)
+constexpr TileCost kCostNT[T_COUNT] = {
+    {256, 256, 1, 1.10, 1.55, 4.0, 6.0}, {256, 160, 1, 1.00, 1.20, 3.0, 5.0},
+    {256, 320, 1, 1.50, 2.35, 4.0, 7.0}, {256, 128, 1, 0.72, 0.88, 3.0, 4.0},
+    {128, 128, 1, 0.42, 0.56, 3.0, 1.5}, {64, 128, 1, 0.29, 0.36, 2.5, 1.2},
+    {64, 64, 2, 0.235, 0.42, 2.5, 0.7}};
+constexpr double kNN160 = 1.2;
+// both operands along their rows (TN)
+constexpr TileCost kCostTN[T_COUNT] = {
+    {256, 256, 1, 1.50, 1.80, 4.0, 6.0}, {256, 160, 1, 1.62, 1.75, 3.0, 5.0},
+    {256, 320, 1, 0, 0, 0, 0},           {256, 128, 1, 0.82, 1.00, 3.0, 4.0},
+    {128, 128, 1, 0.48, 0.62, 3.0, 1.5}, {64, 128, 1, 0.34, 0.42, 2.5, 1.2},
+    {64, 64, 2, 0.26, 0.46, 2.5, 0.7}};
+
+double tile_cost(int layout, TileCfg c, int64_t M, int64_t N, int64_t K, int S) {
     constexpr int64_t kCUs = 256;
-    const int64_t tiles = ((p.M + nt::BM - 1) / nt::BM) * ((p.N + bn - 1) / bn);
-    const int64_t full = tiles / kCUs, rest = tiles % kCUs;
-    const double waves = (double)full + (rest ? 0.5 + 0.5 * (double)rest / kCUs : 0.0);
-    return waves * (double)bn / rate;
+    const TileCost t = layout == LAYOUT_TN ? kCostTN[c] : kCostNT[c];
+    const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S;
+    const double steps = (double)((K + 63) / 64);
+    const int64_t round = kCUs * t.percu, full = tiles / round, rest = tiles % round;
+    double us = (double)full * (t.tf * steps + t.o0 + t.ox * t.percu);
+    if (rest) {
+        const double x = (double)rest / kCUs;   // tiles per CU in the last round
+        const double step = t.percu == 1 ? t.t1 + (t.tf - t.t1) * x : x > 1.0 ? t.tf : t.t1;
+        us += step * steps + t.o0 + t.ox * x;
+    }
+    return layout == LAYOUT_NN && c == T_160 ? us * kNN160 : us;
 }
 
-NtCfg nt_pick(const GemmProblem& p, bool allow320) {
-    const double c160 = nt_cost(p, 160, 0.8), c256 = nt_cost(p, 256, 1.0);
-    const double c320 = allow320 && rows_fit(320, p.ldb) ? nt_cost(p, 320, 0.9) : 1e300;
-    const double other = c160 < c320 ? c160 : c320;
-    if (c256 <= 1.05 * other) return NT_256S;
-    return c160 <= c320 ? NT_160 : NT_320;
+TileCfg pick_tile(int layout, int64_t M, int64_t N, int64_t K, int S, bool allow320,
+                  double* us = nullptr) {
+    TileCfg best = T_256;
+    double least = tile_cost(layout, T_256, M, N, K, S);
+    for (int i = T_160; i < T_COUNT; ++i) {
+        const TileCfg c = (TileCfg)i;
+        if (c == T_320 && !(allow320 && layout == LAYOUT_NT && S == 1)) continue;
+        const double u = tile_cost(layout, c, M, N, K, S);
+        if (u < (best == T_256 ? 0.95 : 1.0) * least) {
+            best = c;
+            least = u;
+        }
+    }
+    if (us) *us = least;
+    return best;
 }
 
-bool nt_kcontig(const GemmProblem& p) { return p.layout == LAYOUT_NT && p.splits <= 1; }
+TileCfg pick_tile(const GemmProblem& p) {
+    return pick_tile(p.layout, p.M, p.N, p.splits > 1 ? p.ksplit : p.K,
+                     p.splits > 1 ? p.splits : 1, rows_fit(320, p.ldb));
+}
 
-// Split-K plan of an NT product written to fp32: the S in 1..kMaxSplits
-// that minimises a two-term cost model, (rounds of 256 concurrent 256 x 160
-// tiles) x (k per split) x (flops per k per tile), plus the fp32 slab
-// traffic of the splits (each written once and read once by the combining
-// pass) counted at equal per-CU flop and chip byte rates (about 4 TFLOP/s
-// per CU against about 4 TB/s).  Splits are taken only when the grid stays
-// within kMaxSplitTiles workgroups, every split covers at least 256 k in
-// whole 64-k steps, and the model gains at least 15%.
-int pick_splits(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
+// Size bound of a product's split-K slabs (and whether it may split at all):
+// the S in 1..kMaxSplits that minimises a two-term cost, (rounds of 256
+// concurrent 256 x 160 tiles) x (k per split) x (flops per k per tile), plus the
+// fp32 slab traffic (each written once and read once) counted at equal per-CU
+// flop and chip byte rates (about 4 TFLOP/s per CU against about 4 TB/s),
+// with at most kMaxSplitTiles workgroups, at least 256 k in whole 64-k steps
+// per split and a gain of 15%.  The workspace is sized by it; the split a
+// product takes (pick_splits) never exceeds it.
+int split_limit(int64_t M, int64_t N, int64_t K) {
     constexpr int64_t kCUs = 256;
     const int64_t tiles = ((M + nt::BM - 1) / nt::BM) * ((N + 159) / 160);
     const double flops_per_k = 2.0 * nt::BM * 160;
     int best = 1;
     double best_cost = (double)((tiles + kCUs - 1) / kCUs) * K * flops_per_k;
     const double plain = best_cost;
-    *ksplit = K;
     for (int S = 2; S <= kMaxSplits; ++S) {
         const int64_t ks = ((K + S - 1) / S + 63) / 64 * 64;
         if (ks < 256 || (K + ks - 1) / ks != S || tiles * S > kMaxSplitTiles) continue;
@@ -736,12 +928,36 @@ int pick_splits(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
         if (cost < best_cost) {
             best = S;
             best_cost = cost;
-            *ksplit = ks;
         }
     }
-    if (best > 1 && best_cost > 0.85 * plain) {
-        best = 1;
-        *ksplit = K;
+    return best > 1 && best_cost > 0.85 * plain ? 1 : best;
+}
+
+// Split-K plan of an NT product written to fp32: the S up to split_limit with
+// the least modelled time of its tiles plus their sum, taken when it gains 5%.
+// Slabs up to 16 MB are read back from the caches (10 TB/s); larger ones cost
+// their reads and the sum's write at 2.5 TB/s (2048 x 1024 in two splits: 8-13
+// us beside the other work of a step).
+int pick_splits(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
+    int best = 1;
+    *ksplit = K;
+    const int limit = split_limit(M, N, K);
+    if (limit <= 1) return 1;
+    double least = 0.0;
+    pick_tile(LAYOUT_NT, M, N, K, 1, false, &least);
+    least *= 0.95;
+    for (int S = 2; S <= limit; ++S) {
+        const int64_t ks = ((K + S - 1) / S + 63) / 64 * 64;
+        if (ks < 256 || (K + ks - 1) / ks != S) continue;
+        double us = 0.0;
+        pick_tile(LAYOUT_NT, M, N, ks, S, false, &us);
+        const double el = (double)M * (double)N;
+        us += 4.0 * S * el <= 16e6 ? 4.0 * S * el / 1e7 : 4.0 * (S + 1) * el / 2.5e6;
+        if (us < least) {
+            best = S;
+            least = us;
+            *ksplit = ks;
+        }
     }
     return best;
 }
@@ -756,29 +972,33 @@ hipError_t launch_pp_cfg(const GemmProblem& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-// The ping-pong kernel for operands contiguous along k (A_K / B_K) or along
-// their rows; split-K launches use the 256 x 160 configuration.
+template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16>
+hipError_t launch_small(const GemmProblem& p, hipStream_t s) {
+    const KArgs a = kargs(p, C::BM, C::BN);
+    const int grid = a.tiles_m * a.tiles_n * a.splits;
+    if (grid == 0) return hipSuccess;
+    hipLaunchKernelGGL((gemm_small_kernel<C, A_K, B_K, EPI, OUT_BF16>), dim3(grid), dim3(C::NT), 0,
+                       s, a);
+    return hipGetLastError();
+}
+
+// Operands contiguous along k (A_K / B_K) or along their rows.
 template <bool A_K, bool B_K, int EPI, bool OUT_BF16>
-hipError_t launch_pp(const GemmProblem& p, hipStream_t s) {
-    if (p.splits > 1) return launch_pp_cfg<nt::Tile160, A_K, B_K, EPI, OUT_BF16>(p, s);
-    if constexpr (A_K && B_K) {
-        switch (nt_pick(p, true)) {
-        case NT_256S: return launch_pp_cfg<nt::Tile256S, A_K, B_K, EPI, OUT_BF16>(p, s);
-        case NT_320: return launch_pp_cfg<nt::Tile320, A_K, B_K, EPI, OUT_BF16>(p, s);
-        default: return launch_pp_cfg<nt::Tile160, A_K, B_K, EPI, OUT_BF16>(p, s);
-        }
-    } else if constexpr (!A_K && !B_K) {
+hipError_t launch_tiles(const GemmProblem& p, hipStream_t s) {
+    switch (pick_tile(p)) {
+    case T_256x128: return launch_small<st::Tile256x128, A_K, B_K, EPI, OUT_BF16>(p, s);
+    case T_128: return launch_small<st::Tile128, A_K, B_K, EPI, OUT_BF16>(p, s);
+    case T_64x128: return launch_small<st::Tile64x128, A_K, B_K, EPI, OUT_BF16>(p, s);
+    case T_64: return launch_small<st::Tile64, A_K, B_K, EPI, OUT_BF16>(p, s);
+    case T_160: return launch_pp_cfg<nt::Tile160, A_K, B_K, EPI, OUT_BF16>(p, s);
+    case T_320:
+        if constexpr (A_K && B_K) return launch_pp_cfg<nt::Tile320, A_K, B_K, EPI, OUT_BF16>(p, s);
+        else return hipErrorInvalidValue;
+    default:
         // both operands row-contiguous: split rings would need more than 256
         // registers per lane (the transposing fragment reads' addresses)
-        return nt_use_256(p) ? launch_pp_cfg<nt::Tile256, A_K, B_K, EPI, OUT_BF16>(p, s)
-                             : launch_pp_cfg<nt::Tile160, A_K, B_K, EPI, OUT_BF16>(p, s);
-    } else {
-        // A contiguous along k, B along its rows (the forward from W as
-        // given): the same model without the 256 x 320 tiles (k-contiguous
-        // only)
-        return nt_pick(p, false) == NT_256S
-                   ? launch_pp_cfg<nt::Tile256S, A_K, B_K, EPI, OUT_BF16>(p, s)
-                   : launch_pp_cfg<nt::Tile160, A_K, B_K, EPI, OUT_BF16>(p, s);
+        if constexpr (!A_K && !B_K) return launch_pp_cfg<nt::Tile256, A_K, B_K, EPI, OUT_BF16>(p, s);
+        else return launch_pp_cfg<nt::Tile256S, A_K, B_K, EPI, OUT_BF16>(p, s);
     }
 }
 
@@ -800,27 +1020,36 @@ bool gemm_supported(int layout, int epi, bool out_bf16) {
 }
 
 const char* gemm_kernel_name(const GemmProblem& p) {
-    static const char* const names[3][3] = {{"gemm_nn", "gemm_nn256", "gemm_nn_splitk"},
-                                            {"gemm_nt", "gemm_nt256", "gemm_nt_splitk"},
-                                            {"gemm_tn", "gemm_tn256", "gemm_tn_splitk"}};
+    static const char* const names[3][T_COUNT] = {
+        {"gemm_nn256", "gemm_nn", "gemm_nn320", "gemm_nn256x128", "gemm_nn128", "gemm_nn64x128",
+         "gemm_nn64"},
+        {"gemm_nt256", "gemm_nt", "gemm_nt320", "gemm_nt256x128", "gemm_nt128", "gemm_nt64x128",
+         "gemm_nt64"},
+        {"gemm_tn256", "gemm_tn", "gemm_tn320", "gemm_tn256x128", "gemm_tn128", "gemm_tn64x128",
+         "gemm_tn64"}};
+    static const char* const split[3] = {"gemm_nn_splitk", "gemm_nt_splitk", "gemm_tn_splitk"};
     const int l = p.layout == LAYOUT_NN ? 0 : p.layout == LAYOUT_NT ? 1 : p.layout == LAYOUT_TN ? 2 : -1;
     if (l < 0) return "gemm_?";
-    if (nt_kcontig(p)) {
-        const NtCfg c = nt_pick(p, true);
-        return c == NT_320 ? "gemm_nt320" : c == NT_256S ? "gemm_nt256" : "gemm_nt";
-    }
-    if (p.layout == LAYOUT_NN && p.splits <= 1)
-        return nt_pick(p, false) == NT_256S ? "gemm_nn256" : "gemm_nn";
-    return names[l][p.splits > 1 ? 2 : nt_use_256(p) ? 1 : 0];
+    return p.splits > 1 ? split[l] : names[l][pick_tile(p)];
 }
 
-bool nn_streams_like_nt(int64_t M, int64_t N) {
-    GemmProblem p;
-    p.layout = LAYOUT_NN;
-    p.M = M;
-    p.N = N;
-    return nt_pick(p, false) == NT_256S;
+double nn_extra_us(int64_t M, int64_t N, int64_t K) {
+    double us = 0.0;
+    const TileCfg c = pick_tile(LAYOUT_NN, M, N, K, 1, false, &us);
+    return c == T_256 ? 0.0 : c == T_160 ? us - us / kNN160 : 0.1 * us;
 }
+
+bool nn_large_tiles(int64_t M, int64_t N) {
+    constexpr int64_t kCUs = 256;
+    auto cost = [&](int64_t bn, double rate) {
+        const int64_t tiles = ((M + nt::BM - 1) / nt::BM) * ((N + bn - 1) / bn);
+        const int64_t full = tiles / kCUs, rest = tiles % kCUs;
+        return ((double)full + (rest ? 0.5 + 0.5 * (double)rest / kCUs : 0.0)) * (double)bn / rate;
+    };
+    return cost(256, 1.0) <= 1.05 * cost(160, 0.8);
+}
+
+int nt_split_limit(int64_t M, int64_t N, int64_t K) { return split_limit(M, N, K); }
 
 int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
     return pick_splits(M, N, K, ksplit);
@@ -829,8 +1058,8 @@ int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
     if (p.M <= 0 || p.N <= 0) return hipSuccess;
     // buffer offsets are 32-bit: one tile's rows of either operand must span
-    // < 2 GiB (256 rows covers the 160- and 256-wide tiles and the 64 k rows
-    // of a row-contiguous operand; nt_pick checks the 320 rows itself)
+    // < 2 GiB (256 rows covers every tile but the 320-wide one and the 64 k
+    // rows of a row-contiguous operand; pick_tile checks the 320 rows itself)
     if (!rows_fit(256, p.lda) || !rows_fit(256, p.ldb)) return hipErrorInvalidValue;
     const bool b16 = p.out_bf16;
     if (p.nparts > kMaxFusedParts || (p.nparts > 1 && (p.splits > 1 || p.own < 0 ||
@@ -847,30 +1076,30 @@ hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
     case LAYOUT_NN:   // X W: A contiguous along k, B = W along its columns
         switch (p.epi) {
         case EPI_NONE:
-            return b16 ? launch_pp<true, false, EPI_NONE, true>(p, s)
-                       : launch_pp<true, false, EPI_NONE, false>(p, s);
+            return b16 ? launch_tiles<true, false, EPI_NONE, true>(p, s)
+                       : launch_tiles<true, false, EPI_NONE, false>(p, s);
         case EPI_BIAS:
-            return b16 ? launch_pp<true, false, EPI_BIAS, true>(p, s)
-                       : launch_pp<true, false, EPI_BIAS, false>(p, s);
+            return b16 ? launch_tiles<true, false, EPI_BIAS, true>(p, s)
+                       : launch_tiles<true, false, EPI_BIAS, false>(p, s);
         case EPI_BIAS_GELU:
-            return b16 ? launch_pp<true, false, EPI_BIAS_GELU, true>(p, s)
-                       : launch_pp<true, false, EPI_BIAS_GELU, false>(p, s);
+            return b16 ? launch_tiles<true, false, EPI_BIAS_GELU, true>(p, s)
+                       : launch_tiles<true, false, EPI_BIAS_GELU, false>(p, s);
         case EPI_GELU_BWD:   // dY W^T with W stored [n][k], times GeLU'(pre)
-            if (b16) return launch_pp<true, false, EPI_GELU_BWD, true>(p, s);
+            if (b16) return launch_tiles<true, false, EPI_GELU_BWD, true>(p, s);
             return hipErrorInvalidValue;
         default:
             return hipErrorInvalidValue;
         }
     case LAYOUT_NT:   // dY W^T with B = W (contiguous along the contraction)
         if (p.epi == EPI_NONE)
-            return b16 ? launch_pp<true, true, EPI_NONE, true>(p, s)
-                       : launch_pp<true, true, EPI_NONE, false>(p, s);
-        if (p.epi == EPI_GELU_BWD && b16) return launch_pp<true, true, EPI_GELU_BWD, true>(p, s);
-        if (p.epi == EPI_BIAS && b16) return launch_pp<true, true, EPI_BIAS, true>(p, s);
-        if (p.epi == EPI_BIAS_GELU && b16) return launch_pp<true, true, EPI_BIAS_GELU, true>(p, s);
+            return b16 ? launch_tiles<true, true, EPI_NONE, true>(p, s)
+                       : launch_tiles<true, true, EPI_NONE, false>(p, s);
+        if (p.epi == EPI_GELU_BWD && b16) return launch_tiles<true, true, EPI_GELU_BWD, true>(p, s);
+        if (p.epi == EPI_BIAS && b16) return launch_tiles<true, true, EPI_BIAS, true>(p, s);
+        if (p.epi == EPI_BIAS_GELU && b16) return launch_tiles<true, true, EPI_BIAS_GELU, true>(p, s);
         return hipErrorInvalidValue;
     case LAYOUT_TN:   // X^T dY: both operands contiguous along their columns
-        if (p.epi == EPI_NONE && !b16) return launch_pp<false, false, EPI_NONE, false>(p, s);
+        if (p.epi == EPI_NONE && !b16) return launch_tiles<false, false, EPI_NONE, false>(p, s);
         return hipErrorInvalidValue;
     default:
         return hipErrorInvalidValue;

@@ -49,16 +49,20 @@ const char* gemm_kernel_name(const GemmProblem& p);
 
 // Split-K plan for an NT product [M, N] over K written to fp32: returns the
 // split count S (1: no split) and the k per split (a multiple of 64; the
-// last split may be shorter).  The plan depends on M, N and K only; S *
-// (256-row tiles) * (160-column tiles) never exceeds kMaxSplitTiles.
-// True when an unsplit NN product [M, N] (B read along its rows, the
-// forward from W stored [k][n]) runs on the 256 x 256 tiles with split copy
-// rings, which stream it as fast as NT from a transposed copy.
-bool nn_streams_like_nt(int64_t M, int64_t N);
-
+// last split may be shorter).  The plan depends on M, N and K only and never
+// exceeds nt_split_limit, by which the slabs are sized; S * (256-row tiles) *
+// (160-column tiles) is at most kMaxSplitTiles there.
 constexpr int kMaxSplits = 16;
 constexpr int64_t kMaxSplitTiles = 512;
+int nt_split_limit(int64_t M, int64_t N, int64_t K);
 int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit);
+// Modelled time (us) that an unsplit product loses by reading B along its rows
+// (NN) instead of along k (NT): none on 256 x 256 tiles, about a tenth on the
+// smaller ones (1003 x 2056 x 1608 and 2048 x 6144 x 1024 measured).
+double nn_extra_us(int64_t M, int64_t N, int64_t K);
+// True when an unsplit NN product [M, N] fills 256 x 256 tiles at least as well
+// as 256 x 160 ones: the workspace keeps no W^T copy for it.
+bool nn_large_tiles(int64_t M, int64_t N);
 
 constexpr int kMaxParts = 64;
 

@@ -127,3 +127,41 @@ def test_fwd_leading_dimensions_and_empty():
     y0 = torch.empty((0, N), device=DEV)
     atp.atp_shard_linear_fwd(m, 0, 0, K, N, 4, x[:0], w, None, 0, y0)
     _sync()
+
+
+@pytest.mark.parametrize("tile,M,N,K", [
+    ("64", 8, 8, 8), ("64", 520, 1160, 72), ("64x128", 1000, 1032, 136), ("128", 520, 6152, 200),
+    ("128", 1000, 2056, 1608), ("256x128", 1000, 6152, 136), ("256x128", 776, 6152, 1000),
+    ("256", 2048, 8000, 328)])
+def test_every_tile_and_layout_integer_bit_exact(tile, M, N, K):
+    """Each tile configuration in the three layouts (NN forward, NT dX, TN
+    dW) at sizes with partial tiles on both sides and a partial last K step
+    (one shorter than the copy ring), against the 64-bit product: integer
+    inputs keep every fp32 sum exact.  The profile names the tile that ran."""
+    m = atp.mesh(1, 1)
+    draw = lambda r, c, t: S.randint_bf16((r, c), 8, t).to(DEV)  # noqa: E731
+    nan = lambda r, c: torch.full((r, c), float("nan"), device=DEV)  # noqa: E731
+    print(f"tile {tile} {M}x{N}x{K}", flush=True)
+    got, names = {}, []
+    atp.atp_profile_enable(1)
+    try:
+        x, w = draw(M, K, 1), draw(K, N, 2)
+        y = nan(M, N)
+        atp.atp_shard_linear_fwd(m, 0, M, K, N, 1, x, w, None, atp.ATP_EPI_NONE, y)
+        got["nn"] = (y, x, w)
+        dy, wt = draw(M, K, 3), draw(N, K, 4)          # dX [M, N] = dY [M, K] W^T [K, N]
+        dx = nan(M, N)
+        atp.atp_shard_linear_bwd(m, 0, M, N, K, 1, draw(M, N, 5), wt, dy, dx, nan(N, K))
+        got["nt"] = (dx, dy, wt.t())
+        xs, dys = draw(K, M, 6), draw(K, N, 7)         # dW [M, N] = X^T [M, K] dY [K, N]
+        dw = nan(M, N)
+        atp.atp_shard_linear_bwd(m, 0, K, M, N, 1, xs, draw(M, N, 8), dys, nan(K, M), dw)
+        got["tn"] = (dw, xs.t(), dys)
+        torch.cuda.synchronize()
+        names = [r["name"] for r in atp.atp_profile_collect(64)]
+    finally:
+        atp.atp_profile_enable(0)
+    for lay, (out, a, b) in got.items():
+        assert any(n.startswith(f"gemm_{lay}{tile}_") for n in names), (lay, names)
+        ref = torch.matmul(a.double(), b.double())
+        assert torch.equal(out.double(), ref), lay
