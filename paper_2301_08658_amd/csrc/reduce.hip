@@ -143,63 +143,77 @@ hipError_t launch_r(const ReduceProblem& p, hipStream_t s) {
 //   db[c] = (((0 + S_0) + S_1) + ...),  S_b over the 64-row block b,
 //   S_b = (((0 + G_b0) + G_b1) + ...)   over its 8-row groups inside [0, T),
 //   G_bg = (((0 + x_r) + x_r+1) + ...)  over the group's rows inside [0, T).
-// A block owns 64 columns: 8 column lanes (8 columns, one 16-byte load per
-// row) x 128 row lanes; row lane ty forms S_b for b = ty, ty + 128, ... one
-// round of 128 blocks at a time, and 64 threads fold each round's S_b into
-// their column's sum in ascending b.  Blocks are renumbered so neighbouring
-// column groups run on the same XCD.
-constexpr int CS_CL = 8;                 // column lanes
-constexpr int CS_COLS = CS_CL * 8;       // columns per block
-constexpr int CS_ROWL = 128;             // row lanes (row blocks per round)
-constexpr int CS_T = CS_CL * CS_ROWL;    // threads per block
+// A block owns 8 CL columns (CL column lanes, one 16-byte load per row each)
+// x CS_T / CL row lanes; a row lane forms the G of one 8-row group (eight
+// loads in flight), a round of CS_T / CL / 8 row blocks at a time.  Through
+// LDS every thread then forms the S_b of one (row block, column) and the first
+// 8 CL threads fold the round's S_b into their columns' sums in ascending b.
+// HBM-bound where the groups fill the chip; a row lane per 64-row block (64
+// loads in sequence) left three quarters of the lanes idle at 2048 rows
+// (2048 x 4096: 25.6 us, one lane per group and 16-column blocks 6.2).
+// CL = 8 reads 128-byte row segments; with fewer than 128 such blocks, CL = 2
+// quadruples the blocks (neighbours, on one XCD, share the lines in its L2).
+// Blocks are renumbered so neighbouring column groups run on the same XCD.
+constexpr int CS_T = 1024;               // threads per block
 
+template <int CL>
 __global__ __launch_bounds__(CS_T) void colsum_kernel(const uint16_t* __restrict__ dy, int64_t ld,
                                                       int64_t T, int64_t N, float* __restrict__ db) {
-    __shared__ float part[CS_ROWL][CS_COLS + 1];
-    const int tx = threadIdx.x % CS_CL;
-    const int ty = threadIdx.x / CS_CL;
+    constexpr int COLS = CL * 8;           // columns per block
+    constexpr int GL = CS_T / CL;          // row lanes: 8-row groups per round
+    constexpr int RB = GL / 8;             // row blocks per round
+    static_assert(RB * COLS == CS_T, "one (row block, column) per thread");
+    __shared__ float gsum[GL][COLS + 1];
+    __shared__ float bsum[RB][COLS + 1];
+    const int tx = threadIdx.x % CL;
+    const int ty = threadIdx.x / CL;
     const int G = gridDim.x, xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
     const int per = G / 8, rem = G % 8;
     const int64_t blk = (xcd < rem) ? xcd * (per + 1) + idx : rem * (per + 1) + (xcd - rem) * per + idx;
-    const int64_t c = blk * CS_COLS + tx * 8;
+    const int64_t c = blk * COLS + tx * 8;
     const int64_t nb = (T + 63) / 64;
-    float acc = 0.0f;                      // column blk * 64 + threadIdx.x (first 64 threads)
-    for (int64_t b0 = 0; b0 < nb; b0 += CS_ROWL) {
-        const int64_t b = b0 + ty;
-        float sb[8];
+    const int sb = threadIdx.x / COLS, sc = threadIdx.x % COLS;
+    float acc = 0.0f;                      // column blk * COLS + threadIdx.x (first COLS threads)
+    for (int64_t b0 = 0; b0 < nb; b0 += RB) {
+        const int64_t r0 = b0 * 64 + ty * 8;
+        float gs[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sb[e] = 0.0f;
-        if (c < N && b < nb) {
-            for (int g = 0; g < 8; ++g) {
-                const int64_t r0 = b * 64 + g * 8;
-                if (r0 >= T) break;
-                float gs[8];
+        for (int e = 0; e < 8; ++e) gs[e] = 0.0f;
+        if (c < N && r0 < T) {
+            u32x4 w[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) gs[e] = 0.0f;
+            for (int i = 0; i < 8; ++i)
+                w[i] = r0 + i < T ? *reinterpret_cast<const u32x4*>(dy + (r0 + i) * ld + c)
+                                  : u32x4{0, 0, 0, 0};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (r0 + i < T) {
-                        float f[8];
-                        unpack8(*reinterpret_cast<const u32x4*>(dy + (r0 + i) * ld + c), f);
+            for (int i = 0; i < 8; ++i)
+                if (r0 + i < T) {
+                    float f[8];
+                    unpack8(w[i], f);
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) gs[e] += f[e];
-                    }
+                    for (int e = 0; e < 8; ++e) gs[e] += f[e];
                 }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) sb[e] += gs[e];
-            }
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) part[ty][tx * 8 + e] = sb[e];
+        for (int e = 0; e < 8; ++e) gsum[ty][tx * 8 + e] = gs[e];
         __syncthreads();
-        if (threadIdx.x < CS_COLS) {
-            const int64_t nr = nb - b0 < CS_ROWL ? nb - b0 : CS_ROWL;
-            for (int r = 0; r < nr; ++r) acc += part[r][threadIdx.x];
+        // the groups of row block b0 + sb inside [0, T)
+        const int64_t left = T - (b0 + sb) * 64;
+        const int ng = left <= 0 ? 0 : left >= 64 ? 8 : (int)((left + 7) / 8);
+        float s = 0.0f;
+#pragma unroll
+        for (int g = 0; g < 8; ++g)
+            if (g < ng) s += gsum[sb * 8 + g][sc];
+        bsum[sb][sc] = s;
+        __syncthreads();
+        if (threadIdx.x < COLS) {
+            const int nr = nb - b0 < RB ? (int)(nb - b0) : RB;
+#pragma unroll 8
+            for (int r = 0; r < nr; ++r) acc += bsum[r][threadIdx.x];
         }
-        __syncthreads();
     }
-    if (threadIdx.x < CS_COLS) {
-        const int64_t col = blk * CS_COLS + threadIdx.x;
+    if (threadIdx.x < COLS) {
+        const int64_t col = blk * COLS + threadIdx.x;
         if (col < N) db[col] = acc;
     }
 }
@@ -283,9 +297,14 @@ hipError_t launch_colsum_finish(const float* part, int64_t ldp, int64_t nb, int6
 hipError_t launch_colsum(const void* dy, int64_t ld, int64_t T, int64_t N, float* db,
                          hipStream_t s) {
     if (N <= 0) return hipSuccess;
-    const int64_t blocks = (N + CS_COLS - 1) / CS_COLS;
-    hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)blocks), dim3(CS_T), 0, s,
-                       static_cast<const uint16_t*>(dy), ld, T, N, db);
+    const uint16_t* y = static_cast<const uint16_t*>(dy);
+    const int64_t wide = (N + 63) / 64;
+    if (wide >= 128)
+        hipLaunchKernelGGL((colsum_kernel<8>), dim3((unsigned)wide), dim3(CS_T), 0, s, y, ld, T, N,
+                           db);
+    else
+        hipLaunchKernelGGL((colsum_kernel<2>), dim3((unsigned)((N + 15) / 16)), dim3(CS_T), 0, s, y,
+                           ld, T, N, db);
     return hipGetLastError();
 }
 

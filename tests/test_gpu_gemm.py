@@ -165,3 +165,18 @@ def test_every_tile_and_layout_integer_bit_exact(tile, M, N, K):
         assert any(n.startswith(f"gemm_{lay}{tile}_") for n in names), (lay, names)
         ref = torch.matmul(a.double(), b.double())
         assert torch.equal(out.double(), ref), lay
+
+
+@pytest.mark.parametrize("T,N", [(1, 8), (4099, 40), (130, 72), (5000, 8200), (1024, 8192)])
+def test_bias_gradient_rounds_and_widths_integer_bit_exact(T, N):
+    """db alone (the column sum) over one and several rounds of row blocks,
+    in 16-column blocks and, from 128 of them on, 64-column blocks, with
+    partial 8-row groups, row blocks and column blocks."""
+    print(f"column sum {T}x{N}", flush=True)
+    dy = S.randint_bf16((T, N), 9, 1).to(DEV)
+    x, w = S.randint_bf16((T, 8), 9, 2).to(DEV), S.randint_bf16((8, N), 9, 3).to(DEV)
+    db = torch.full((N,), float("nan"), device=DEV)
+    atp.atp_shard_linear_bwd(atp.mesh(1, 1), 0, T, 8, N, 1, x, w, dy,
+                             torch.empty((T, 8), device=DEV), torch.empty((8, N), device=DEV), db)
+    _sync()
+    assert torch.equal(db.double(), dy.double().sum(0))
