@@ -842,21 +842,23 @@ bool rows_fit(int64_t rows, int64_t ld) { return rows * ld * 2 <= kMaxSpan; }
 // Tile configuration of a product: the one with the least modelled time.  A
 // configuration's tiles run in rounds of 256 * percu; a K step of 64 takes t1
 // us while the CUs hold at most one tile each and few are busy, tf with every
-// CU full (between them linearly in the busy share where a CU holds one tile;
-// two tiles on any one CU make it tf), and a round adds o0 + ox * (tiles / 256)
+// CU full (between them with the square of the busy share where a CU holds one
+// tile; two tiles on any one CU make it tf), and a round adds o0 + ox * (tiles / 256)
 // us of prologue and output.  Fitted to launches back to back with operand A
 // from HBM, as in a step (tiles x K steps: us [model]): 256 x 256: 32 x 128 148
-// [152], 256 x 64 103 [109]; 256 x 128: 64 x 128 98 [101], 192 x 128 104 [113], 512 x
-// 64 123 [127]; 128 x 128: 64 x 64 28 [32], 192 x 192 106 [105], 1024 x 64 145 [161];
-// 64 x 128: 256 x 128 49 [50], 128 x 64 22 [24]; 64 x 64: 256 x 64 18 [18],
-// 1024 x 64 64 [62].  A smaller tile has to beat the large ones by 5%: they
-// leave CUs to the reductions that run beside a one-round product.
+// [146], 256 x 64 103 [109]; 256 x 128: 64 x 128 98 [97], 192 x 128 104 [110], 512 x
+// 64 123 [127]; 128 x 128: 64 x 64 28 [31], 192 x 192 106 [100], 1024 x 64 145 [161];
+// 64 x 128: 256 x 128 49 [50], 128 x 64 22 [21]; 64 x 64: 256 x 64 18 [18], 1024 x
+// 64 64 [62].  256 x 160 is charged more than alone (256 x 320 368 [408]): it
+// leaves no CU to a reduction beside it (4096 x 2560 x 20480 in the wide layer's
+// step: 727 us, 435 on 160 tiles of 256 x 256).  For the same reason a smaller
+// tile has to beat the 256 x 256 ones by 5%.
 enum TileCfg { T_256, T_160, T_320, T_256x128, T_128, T_64x128, T_64, T_COUNT };
 
 struct TileCost { int bm, bn, percu; double t1, tf, o0, ox; };
 // k-contiguous A (NT, and NN, whose 160-wide tiles are slower)
 constexpr TileCost kCostNT[T_COUNT] = {
-    {256, 256, 1, 1.10, 1.55, 4.0, 6.0}, {256, 160, 1, 1.00, 1.20, 3.0, 5.0},
+    {256, 256, 1, 1.10, 1.55, 4.0, 6.0}, {256, 160, 1, 1.00, 1.25, 3.0, 5.0},
     {256, 320, 1, 1.50, 2.35, 4.0, 7.0}, {256, 128, 1, 0.72, 0.88, 3.0, 4.0},
     {128, 128, 1, 0.42, 0.56, 3.0, 1.5}, {64, 128, 1, 0.29, 0.36, 2.5, 1.2},
     {64, 64, 2, 0.235, 0.42, 2.5, 0.7}};
@@ -877,7 +879,7 @@ double tile_cost(int layout, TileCfg c, int64_t M, int64_t N, int64_t K, int S) 
     double us = (double)full * (t.tf * steps + t.o0 + t.ox * t.percu);
     if (rest) {
         const double x = (double)rest / kCUs;   // tiles per CU in the last round
-        const double step = t.percu == 1 ? t.t1 + (t.tf - t.t1) * x : x > 1.0 ? t.tf : t.t1;
+        const double step = t.percu == 1 ? t.t1 + (t.tf - t.t1) * x * x : x > 1.0 ? t.tf : t.t1;
         us += step * steps + t.o0 + t.ox * x;
     }
     return layout == LAYOUT_NN && c == T_160 ? us * kNN160 : us;
