@@ -170,6 +170,30 @@ struct TileDma2 {
             dma::lds_dma16(r1, t1 + ins * 64 * 8, off1 + r * st1, 0u);
         }
     }
+    // The same tile in four rounds (r = 0..3) that the main loops spread over
+    // their score products, one per head-dimension slice: a wave stands at a
+    // copy instruction while the CU's memory path is busy, so a burst of all
+    // eight copies of every wave at the start of a step held the first
+    // products up for as long as the path needs for the tile (wide share
+    // forward 67 -> 60 us and backward 224 -> 206, GPT-3 share 33 -> 27.5 and 86 ->
+    // 78; the second operand's copies during the second products: 63 and 219).
+    struct Rounds {
+        dma::u32x4 r0, r1;
+        uint16_t *t0, *t1;
+    };
+    __device__ __forceinline__ Rounds rounds(const uint16_t* b0, int64_t ld0, const uint16_t* b1,
+                                             int64_t ld1, int64_t tok0, int n0, int seq,
+                                             uint16_t* t0, uint16_t* t1) const {
+        const int64_t left = seq - n0;
+        const int64_t vr = left < 0 ? 0 : (left < 64 ? left : 64);
+        return Rounds{dma::rsrc_words(b0 + (tok0 + n0) * ld0, vr * ld0 * 2),
+                      dma::rsrc_words(b1 + (tok0 + n0) * ld1, vr * ld1 * 2), t0, t1};
+    }
+    __device__ __forceinline__ void round(const Rounds& q, int r, int wave) const {
+        const int ins = wave + NWAVE * r;
+        dma::lds_dma16(q.r0, q.t0 + ins * 64 * 8, off0 + r * st0, 0u);
+        dma::lds_dma16(q.r1, q.t1 + ins * 64 * 8, off1 + r * st1, 0u);
+    }
 };
 
 // RB row blocks of 16 queries per wave (query tile of 64 RB rows): every K
@@ -253,9 +277,9 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnAr
             const uint16_t* ks_ = buf[i & 1][0];
             const uint16_t* vs_ = buf[i & 1][1];
             // the other buffer was last read in step i - 1, before its barrier
-            if (i + 1 < mine)
-                cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
-                         buf[(i + 1) & 1][0], buf[(i + 1) & 1][1], wave);
+            const bool more = i + 1 < mine;
+            const auto next = cp.rounds(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
+                                        buf[(i + 1) & 1][0], buf[(i + 1) & 1][1]);
 
             // S = Q K^T for RB x 16 rows x 64 keys (raw scores); the 4 RB
             // accumulators advance together over the head dimension, so
@@ -275,6 +299,7 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnAr
                     for (int r = 0; r < RB; ++r)
                         s[r][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qf[r][ks], s[r][j],
                                                                           0, 0, 0);
+                    if (j == 3 && more) cp.round(next, ks, wave);
                 }
             // causal mask (and keys past the sequence): only key tiles that
             // reach past the tile's first row and a ragged last tile have
@@ -523,11 +548,10 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dkv_kernel(AttnBw
             const uint16_t* qs = qb[buf][0];
             const uint16_t* ds_ = qb[buf][1];
             // the other buffers were last read in step i - 1, before its barrier
-            if (i + 1 < mine) {
-                cp.issue(qbase, a.ldq, dobase, a.lddo, tok0, (qt + 1) * BM, a.seq, qb[buf ^ 1][0],
-                         qb[buf ^ 1][1], wave);
-                load_rows(qt + 1, l2r, dlr);
-            }
+            const bool more = i + 1 < mine;
+            const auto next = cp.rounds(qbase, a.ldq, dobase, a.lddo, tok0, (qt + 1) * BM, a.seq,
+                                        qb[buf ^ 1][0], qb[buf ^ 1][1]);
+            if (more) load_rows(qt + 1, l2r, dlr);
             // S^T and dP^T: lane holds (key = kabs, query = 16 j + 4 g + e).
             // The eight accumulators of the four 16-query blocks advance
             // together over the head dimension, so consecutive products are
@@ -549,6 +573,7 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dkv_kernel(AttnBw
                     dsv[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                         *reinterpret_cast<const bf16x8*>(ds_ + 16 * j * D + boff[ks]), vf[ks],
                         dsv[j], 0, 0, 0);
+                    if (j == 3 && more) cp.round(next, ks, wave);
                 }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
@@ -709,9 +734,9 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dq_kernel(AttnBwd
             const int kt = k0 + i;
             const uint16_t* ks_ = kb[i & 1][0];
             const uint16_t* vs_ = kb[i & 1][1];
-            if (i + 1 < mine)
-                cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
-                         kb[(i + 1) & 1][0], kb[(i + 1) & 1][1], wave);
+            const bool more = i + 1 < mine;
+            const auto next = cp.rounds(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
+                                        kb[(i + 1) & 1][0], kb[(i + 1) & 1][1]);
             // S and dP: lane holds (query = qabs[r], key = 16 j + 4 g + e); a
             // key tile reaching past the tile's first row, or a ragged one,
             // has masked keys
@@ -746,6 +771,7 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dq_kernel(AttnBwd
                             dacc[r][jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                 vf, of[r][ks], dacc[r][jj], 0, 0, 0);
                         }
+                        if (j0 == 0 && jj == JG - 1 && more) cp.round(next, ks, wave);
                     }
 #pragma unroll
                 for (int jj = 0; jj < JG; ++jj)
