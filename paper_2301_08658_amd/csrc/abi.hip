@@ -545,21 +545,76 @@ const char* const kLinearName[4] = {"qkv", "out", "fc1", "fc2"};
 // delays its last tiles (measured: a second GEMM stream, or transposes and
 // column sums beside the GEMMs, made the step 3-6% slower); only the
 // reductions, which overlap by design, run beside them.
+//
+// Reductions too short to gain from that stay on cs, between their product
+// and the next: handing one over costs two host calls and a dependency
+// between two hardware queues, more than a reduction of 8 MB (under 2 us at
+// HBM rate) could hide (h = 512 layer, forward and backward of 256 tokens in 2
+// chunks: 640 us on two streams, 365 so; with 40 MB instead the h = 12288 forward,
+// whose chunk reductions move 28-38 MB, took 1414 us instead of 1210).
+// They still come after everything queued on ms before the call, and ms after
+// the call is ordered after them.  Under graph capture every reduction runs
+// on ms (ms joins the capture when it first waits for a product).
+constexpr double kInlineBytes = 8e6;   // one chunk's reduction, read and written
 struct Streams {
     hipStream_t cs, ms;
+    bool may_inline = false;   // two streams and no capture
+    bool ms_used = false, cs_joined = false;
+    hipEvent_t* ev = nullptr;  // three events: ms before the call, after it, cs after it
     Streams(void* c, void* m) : cs(static_cast<hipStream_t>(c)), ms(static_cast<hipStream_t>(m)) {}
 
-    // everything already queued on cs happens before the block's work
-    atp_status begin(hipEvent_t start) const {
-        HIP_CHECK(hipEventRecord(start, cs), "hipEventRecord");
-        if (ms != cs) HIP_CHECK(hipStreamWaitEvent(ms, start, 0), "hipStreamWaitEvent");
+    atp_status begin(hipEvent_t* events) {
+        ev = events;
+        if (ms == cs) return ATP_OK;
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        HIP_CHECK(hipStreamIsCapturing(cs, &cap), "hipStreamIsCapturing");
+        may_inline = cap == hipStreamCaptureStatusNone;
         return ATP_OK;
     }
-    // cs is ordered after all of the block's work on ms
-    atp_status end(hipEvent_t ms_end) const {
-        if (ms != cs) {
-            HIP_CHECK(hipEventRecord(ms_end, ms), "hipEventRecord");
-            HIP_CHECK(hipStreamWaitEvent(cs, ms_end, 0), "hipStreamWaitEvent");
+    // Queued first when some reduction will run on ms: ms waits for what cs
+    // held before the call.  (Its first product's event would order it as
+    // well; this early packet has ms's queue awake by then: 945 against 934 us
+    // for a 922 us forward and backward.)
+    atp_status open(hipEvent_t start) const {
+        if (ms == cs) return ATP_OK;
+        HIP_CHECK(hipEventRecord(start, cs), "hipEventRecord");
+        HIP_CHECK(hipStreamWaitEvent(ms, start, 0), "hipStreamWaitEvent");
+        return ATP_OK;
+    }
+    // whether chunk reductions of `parts` partials over rows x cols run on cs
+    bool inlined(int64_t rows, int64_t cols, int parts, bool b16) const {
+        return may_inline &&
+               (double)rows * (double)cols * (parts * (b16 ? 2.0 : 4.0) + 2.0) <= kInlineBytes;
+    }
+    // The stream of a reduction whose product was just queued on st (cs, when
+    // the reduction is inlined): ordered after it; `done` marks the product.
+    atp_status reduction(bool inl, hipStream_t st, hipEvent_t done, hipStream_t* rs) {
+        *rs = cs;
+        if (ms == cs) return ATP_OK;
+        if (inl) {
+            if (!cs_joined) {
+                HIP_CHECK(hipEventRecord(ev[0], ms), "hipEventRecord");
+                HIP_CHECK(hipStreamWaitEvent(cs, ev[0], 0), "hipStreamWaitEvent");
+                cs_joined = true;
+            }
+            return ATP_OK;
+        }
+        HIP_CHECK(hipEventRecord(done, st), "hipEventRecord");
+        HIP_CHECK(hipStreamWaitEvent(ms, done, 0), "hipStreamWaitEvent");
+        ms_used = true;
+        *rs = ms;
+        return ATP_OK;
+    }
+    // cs is ordered after all of the block's work on ms, and ms after the
+    // reductions on cs
+    atp_status end() const {
+        if (ms_used) {
+            HIP_CHECK(hipEventRecord(ev[1], ms), "hipEventRecord");
+            HIP_CHECK(hipStreamWaitEvent(cs, ev[1], 0), "hipStreamWaitEvent");
+        }
+        if (cs_joined) {
+            HIP_CHECK(hipEventRecord(ev[2], cs), "hipEventRecord");
+            HIP_CHECK(hipStreamWaitEvent(ms, ev[2], 0), "hipStreamWaitEvent");
         }
         return ATP_OK;
     }
@@ -1056,39 +1111,44 @@ atp_status weight_grads(const atp_shard& g, bool kn, const void* X, int64_t ldx,
 
 // One reduced product of the chain, chunked (Sec. 4.1): chunk c's GEMM on
 // cs writes the own partial rows (or, for a group of one, the whole output
-// with its epilogue in one launch), and ms reduces the group's partials of
-// those rows with the epilogue as soon as they are written.  `done` is
-// recorded after the last chunk's reduction (on ms), or after the single
-// launch (on cs).  make(A_rows, C_rows, ldc, b16, epi, M) builds the product;
+// with its epilogue in one launch), and the group's partials of those rows are
+// reduced with the epilogue as soon as they are written.  `*done` is recorded
+// after the last chunk's reduction when that runs on ms, else set to NULL (the
+// output is ordered on cs).  make(A_rows, C_rows, ldc, b16, epi, M) builds the product;
 // with a slab, a chunk product with too few tiles is split over k there.
 template <class Make>
-atp_status chained_linear(const Streams& S, int red_size, int red_index, void* const* parts,
+atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* parts,
                           int64_t ldp, bool pb16, const void* A, int64_t lda, int64_t ncols,
                           int epi, const void* bias, const void* pre_in, void* out, int64_t ldo,
-                          int64_t T, int32_t chunks, hipEvent_t* ev_chunk, hipEvent_t done,
+                          int64_t T, int32_t chunks, hipEvent_t* ev_chunk, hipEvent_t* done,
                           Make make, float* slab = nullptr) {
     if (red_size == 1) {
         atp::GemmProblem p = make(A, out, ldo, true, epi, T);
         p.bias = bias;
         p.pre_in = pre_in;
-        ATP_CHECK(run_gemm(p, S.cs));
-        HIP_CHECK(hipEventRecord(done, S.cs), "hipEventRecord");
-        return ATP_OK;
+        *done = nullptr;
+        return run_gemm(p, S.cs);
     }
     const int64_t mc = T / chunks;
+    const bool inl = S.inlined(mc, ncols, red_size, pb16);
+    if (!inl && !S.ms_used) ATP_CHECK(S.open(*done));   // (*done is recorded again below)
     void* own = parts[red_index];
     for (int32_t c = 0; c < chunks; ++c) {
         const int64_t r0 = (int64_t)c * mc;
         atp::GemmProblem p = make(static_cast<const uint16_t*>(A) + r0 * lda,
                                   row_ptr(own, r0, ldp, pb16), ldp, pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
-        HIP_CHECK(hipEventRecord(ev_chunk[c], S.cs), "hipEventRecord");
-        HIP_CHECK(hipStreamWaitEvent(S.ms, ev_chunk[c], 0), "hipStreamWaitEvent");
+        hipStream_t rs = nullptr;
+        ATP_CHECK(S.reduction(inl, S.cs, ev_chunk[c], &rs));
         atp::ReduceProblem r = reduce_problem(red_size, parts, ldp, r0, mc, ncols, epi, bias,
                                               pre_in, out, ldo, true, nullptr, pb16);
-        ATP_CHECK(run_reduce(r, S.ms));
+        ATP_CHECK(run_reduce(r, rs));
     }
-    HIP_CHECK(hipEventRecord(done, S.ms), "hipEventRecord");
+    if (inl || S.ms == S.cs) {
+        *done = nullptr;
+        return ATP_OK;
+    }
+    HIP_CHECK(hipEventRecord(*done, S.ms), "hipEventRecord");
     return ATP_OK;
 }
 
@@ -1220,23 +1280,18 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
 
     Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
-    // [0] start  [1] comm end  [2] second lane forked  [3] second lane
-    // joined, then per linear per chunk GEMM-done, then fc1 reduce-done per
-    // chunk
-    const size_t n_ev = 4 + 4 * (size_t)chunks + (size_t)chunks;
+    // [0..2] the streams'  [3] second lane forked  [4] second lane joined  [5]
+    // start, then per linear per chunk GEMM-done, then fc1 reduce-done per chunk
+    const size_t n_ev = 6 + 4 * (size_t)chunks + (size_t)chunks;
     ATP_CHECK(sync_events(n_ev, &ev));
-    hipEvent_t* ev_gemm = ev + 4;
-    hipEvent_t* ev_red1 = ev + 4 + 4 * chunks;
-    ATP_CHECK(S.begin(ev[0]));
+    hipEvent_t* ev_gemm = ev + 6;
+    hipEvent_t* ev_red1 = ev + 6 + 4 * chunks;
+    ATP_CHECK(S.begin(ev));
     // A second compute lane for the chunk products, only when the caller
     // overlaps at all (comm_stream != compute_stream) and outside graph
     // capture (captures stay on the streams the caller gave)
     hipStream_t lane2 = nullptr;
-    if (S.ms != S.cs && chunks > 1) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        HIP_CHECK(hipStreamIsCapturing(S.cs, &cap), "hipStreamIsCapturing");
-        if (cap == hipStreamCaptureStatusNone) ATP_CHECK(second_lane(&lane2));
-    }
+    if (S.may_inline && chunks > 1) ATP_CHECK(second_lane(&lane2));
     bool lane2_used = false;
 
     uint16_t* wt[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -1282,11 +1337,20 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     const int64_t lda_in[4] = {io->ldx, io->lda, io->ldx, io->ld_h};
     void* outp[4] = {io->qkv, io->o, io->h, io->z};
     const int64_t ldo[4] = {io->ld_qkv, io->ld_o, io->ld_h, io->ld_z};
-    const bool fc1_reduced = P.g[2].red_size > 1;
+    bool inl[4];
+    for (int L = 0; L < 4; ++L)
+        inl[L] = S.inlined(mc, P.g[L].n_loc, P.g[L].red_size, pb16);
+    for (int L = 0; L < 4; ++L)
+        if (P.g[L].red_size > 1 && !inl[L]) {
+            ATP_CHECK(S.open(ev[5]));
+            break;
+        }
+    // fc1's H is reduced on ms
+    const bool fc1_reduced = P.g[2].red_size > 1 && S.ms != S.cs && !inl[2];
 
     // fc2 reads H: wait for fc1's reduced chunk c (the comm stream runs in
-    // order, so chunk chunks-1 means all of H); fc1's single launch is
-    // ordered before fc2 on the compute stream already
+    // order, so chunk chunks-1 means all of H); on the compute stream fc1's
+    // single launch or reductions are ordered before fc2 already
     auto wait_h = [&](int c, hipStream_t st) -> atp_status {
         if (fc1_reduced) HIP_CHECK(hipStreamWaitEvent(st, ev_red1[c], 0), "hipStreamWaitEvent");
         return ATP_OK;
@@ -1311,30 +1375,31 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                          lda_in[L], row_ptr(own, r0, io->ldp[L], pb16),
                                          io->ldp[L], pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, st));
-        hipEvent_t e = ev_gemm[L * chunks + c];
-        HIP_CHECK(hipEventRecord(e, st), "hipEventRecord");
-        HIP_CHECK(hipStreamWaitEvent(S.ms, e, 0), "hipStreamWaitEvent");
+        hipStream_t rs = nullptr;
+        ATP_CHECK(S.reduction(inl[L], st, ev_gemm[L * chunks + c], &rs));
         atp::ReduceProblem r = reduce_problem(
             g.red_size, io->partials[L], io->ldp[L], r0, mc, g.n_loc,
             L == 2 ? atp::EPI_BIAS_GELU : atp::EPI_BIAS, w->b[L], nullptr, outp[L], ldo[L], true,
             L == 2 ? io->pre : nullptr, pb16);
-        ATP_CHECK(run_reduce(r, S.ms));
-        if (L == 2) HIP_CHECK(hipEventRecord(ev_red1[c], S.ms), "hipEventRecord");
+        ATP_CHECK(run_reduce(r, rs));
+        if (L == 2 && fc1_reduced) HIP_CHECK(hipEventRecord(ev_red1[c], rs), "hipEventRecord");
         return ATP_OK;
     };
     // Odd chunks go to the second lane unless the chunk products split over
     // k (the splits of every chunk share one slab region, so they stay in
-    // order on one stream); the lane first waits for everything queued on
-    // compute_stream so far (fc1's output, the W^T copy).
+    // order on one stream) or their reductions stay on compute_stream; the
+    // lane first waits for everything queued on compute_stream so far (fc1's
+    // output, the W^T copy).
     auto linear = [&](int L) -> atp_status {
         const atp_shard& g = P.g[L];
         if (g.red_size == 1) return unchunked(L);
         ATP_CHECK(need_wt(L));
         int64_t ks = 0;
-        const bool two = lane2 && (!slab || atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) <= 1);
+        const bool two = lane2 && !inl[L] &&
+                         (!slab || atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) <= 1);
         if (two) {
-            HIP_CHECK(hipEventRecord(ev[2], S.cs), "hipEventRecord");
-            HIP_CHECK(hipStreamWaitEvent(lane2, ev[2], 0), "hipStreamWaitEvent");
+            HIP_CHECK(hipEventRecord(ev[3], S.cs), "hipEventRecord");
+            HIP_CHECK(hipStreamWaitEvent(lane2, ev[3], 0), "hipStreamWaitEvent");
             lane2_used = true;
         }
         for (int c = 0; c < chunks; ++c) ATP_CHECK(chunk(L, c, two && (c & 1) ? lane2 : S.cs));
@@ -1352,10 +1417,10 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     for (int L : order) ATP_CHECK(linear(L));
     if (lane2_used) {
         // compute_stream is ordered after the second lane's products
-        HIP_CHECK(hipEventRecord(ev[3], lane2), "hipEventRecord");
-        HIP_CHECK(hipStreamWaitEvent(S.cs, ev[3], 0), "hipStreamWaitEvent");
+        HIP_CHECK(hipEventRecord(ev[4], lane2), "hipEventRecord");
+        HIP_CHECK(hipStreamWaitEvent(S.cs, ev[4], 0), "hipStreamWaitEvent");
     }
-    return S.end(ev[1]);
+    return S.end();
 }
 
 atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t tokens, int64_t h,
@@ -1414,13 +1479,13 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
 
     Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
-    // [0] start  [1] comm end  [2..3] unused, then per linear per chunk
-    // GEMM-done, then fc2 reduce-done per chunk
+    // [0..2] the streams'  [3] start, then per linear per chunk GEMM-done, then
+    // fc2 reduce-done per chunk
     const size_t n_ev = 4 + 4 * (size_t)chunks + (size_t)chunks;
     ATP_CHECK(sync_events(n_ev, &ev));
     hipEvent_t* ev_gemm = ev + 4;
     hipEvent_t* ev_red2 = ev + 4 + 4 * chunks;
-    ATP_CHECK(S.begin(ev[0]));
+    ATP_CHECK(S.begin(ev));
 
     // X^T pieces: 0 = x (QKV and fc1), 1 = attention block (out), 2 = H (fc2)
     const int xsrc[4] = {0, 1, 0, 2};
@@ -1449,11 +1514,20 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     const int64_t ld_dy[4] = {io->ld_dqkv, io->ld_do, io->ld_h, io->ld_dz};
     void* dXo[4] = {io->dx_qkv, io->d_attn, io->dx_fc1, io->dh_pre};
     const int64_t ld_dxo[4] = {io->ld_dx_qkv, io->ld_d_attn, io->ld_dx_fc1, io->ld_h};
-    const bool fc2_reduced = P.g[3].bwd_size > 1;
+    bool inl[4];
+    for (int L = 0; L < 4; ++L)
+        inl[L] = S.inlined(mc, P.g[L].k_loc, P.g[L].bwd_size, pb16);
+    for (int L = 0; L < 4; ++L)
+        if (P.g[L].bwd_size > 1 && !inl[L]) {
+            ATP_CHECK(S.open(ev[3]));
+            break;
+        }
+    // fc2's dX is reduced on ms
+    const bool fc2_reduced = P.g[3].bwd_size > 1 && S.ms != S.cs && !inl[3];
 
     // fc1's dY is dh_pre: wait for fc2's reduced chunk c (chunk chunks-1
-    // means all of it, the comm stream runs in order); fc2's single dX
-    // launch is ordered before fc1 on the compute stream already
+    // means all of it, the comm stream runs in order); on the compute stream
+    // fc2's single dX launch or reductions are ordered before fc1 already
     auto wait_dpre = [&](int c) -> atp_status {
         if (fc2_reduced) HIP_CHECK(hipStreamWaitEvent(S.cs, ev_red2[c], 0), "hipStreamWaitEvent");
         return ATP_OK;
@@ -1501,15 +1575,14 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                         ld_dy[L], row_ptr(own, r0, io->ld_dxp[L], pb16),
                                         io->ld_dxp[L], pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
-        hipEvent_t e = ev_gemm[L * chunks + c];
-        HIP_CHECK(hipEventRecord(e, S.cs), "hipEventRecord");
-        HIP_CHECK(hipStreamWaitEvent(S.ms, e, 0), "hipStreamWaitEvent");
+        hipStream_t rs = nullptr;
+        ATP_CHECK(S.reduction(inl[L], S.cs, ev_gemm[L * chunks + c], &rs));
         atp::ReduceProblem r = reduce_problem(
             g.bwd_size, io->dx_partials[L], io->ld_dxp[L], r0, mc, g.k_loc,
             L == 3 ? atp::EPI_GELU_BWD : atp::EPI_NONE, nullptr, L == 3 ? io->pre : nullptr,
             dXo[L], ld_dxo[L], true, nullptr, pb16);
-        ATP_CHECK(run_reduce(r, S.ms));
-        if (L == 3) HIP_CHECK(hipEventRecord(ev_red2[c], S.ms), "hipEventRecord");
+        ATP_CHECK(run_reduce(r, rs));
+        if (L == 3 && fc2_reduced) HIP_CHECK(hipEventRecord(ev_red2[c], rs), "hipEventRecord");
         return ATP_OK;
     };
     auto dx = [&](int L) -> atp_status {
@@ -1523,19 +1596,12 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     auto dw = [&](int L) -> atp_status {
         const atp_shard& g = P.g[L];
         if (L == 2) ATP_CHECK(wait_dpre(chunks - 1));
-        if (io->db[L] && !ws)
-            ATP_CHECK(run_colsum(dY[L], ld_dy[L], tokens, g.n_loc, io->db[L], S.cs));
-        if (!ws) {
-            atp::GemmProblem p =
-                kn ? gemm_problem(atp::LAYOUT_TN, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L],
-                                  w->ldw[L], false, atp::EPI_NONE, g.k_loc, g.n_loc, tokens)
-                   : gemm_problem(atp::LAYOUT_TN, dY[L], ld_dy[L], Xin[L], ldx_in[L], io->dw[L],
-                                  w->ldw[L], false, atp::EPI_NONE, g.n_loc, g.k_loc, tokens);
-            return run_gemm(p, S.cs);
-        }
+        const int xi = xsrc[L];
+        if (!ws)
+            return weight_grads(g, kn, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L], w->ldw[L],
+                                io->db[L], tokens, S.cs);
         // X^T once per source (x serves QKV and fc1), dY^T, then the NT
         // product over the tokens
-        const int xi = xsrc[L];
         const int64_t tp = ws_pitch(tokens);
         if (!xt_done[xi]) {
             ATP_CHECK(run_transpose(Xin[L], ldx_in[L], tokens, g.k_loc, xt[xi], tp, S.cs));
@@ -1567,7 +1633,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         return P.g[i].k_loc * P.g[i].n_loc > P.g[j].k_loc * P.g[j].n_loc;
     });
     for (int L : order) ATP_CHECK(dw(L));
-    return S.end(ev[1]);
+    return S.end();
 }
 
 atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t batch,
@@ -1623,10 +1689,11 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
 
     Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
-    // [0] start  [1] comm end  [2] QKV reduced  [3] out-proj done, then the
-    // chunk events of QKV and of out-proj
-    ATP_CHECK(sync_events(4 + 2 * (size_t)chunks, &ev));
-    ATP_CHECK(S.begin(ev[0]));
+    // [0..2] the streams'  [3] QKV reduced  [4] out-proj done, then the chunk
+    // events of QKV and of out-proj
+    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
+    ATP_CHECK(S.begin(ev));
+    hipEvent_t qkv_done = ev[3], o_done = ev[4];
     auto make = [&](int L) {
         return [&, L](const void* A, void* C, int64_t ldc, bool b16, int epi, int64_t M) {
             const int64_t lda = L == 0 ? io->ldx : io->ld_attn;
@@ -1646,9 +1713,9 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     ATP_CHECK(need_wt(0));
     ATP_CHECK(chained_linear(S, gq.red_size, gq.red_index, io->qkv_partials, io->ldp_qkv, pb16,
                              io->x_loc, io->ldx, gq.n_loc, atp::EPI_BIAS, w->b[0], nullptr,
-                             io->qkv, io->ld_qkv, T, chunks, ev + 4, ev[2], make(0), slab));
+                             io->qkv, io->ld_qkv, T, chunks, ev + 5, &qkv_done, make(0), slab));
     // a causal sequence spans chunks: the core waits for the whole QKV block
-    HIP_CHECK(hipStreamWaitEvent(S.cs, ev[2], 0), "hipStreamWaitEvent");
+    if (qkv_done) HIP_CHECK(hipStreamWaitEvent(S.cs, qkv_done, 0), "hipStreamWaitEvent");
     if (T > 0) {
         atp::AttentionProblem p;
         p.qkv = io->qkv;
@@ -1670,8 +1737,8 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     ATP_CHECK(need_wt(1));
     ATP_CHECK(chained_linear(S, go.red_size, go.red_index, io->o_partials, io->ldp_o, pb16,
                              io->attn, io->ld_attn, go.n_loc, atp::EPI_BIAS, w->b[1], nullptr,
-                             io->o, io->ld_o, T, chunks, ev + 4 + chunks, ev[3], make(1), slab));
-    return S.end(ev[1]);
+                             io->o, io->ld_o, T, chunks, ev + 5 + chunks, &o_done, make(1), slab));
+    return S.end();
 }
 
 atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t batch,
@@ -1752,10 +1819,11 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
 
     Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
-    // [0] start  [1] comm end  [2] d_attn reduced  [3] QKV dX done, then the
-    // chunk events of out-proj's dX and of QKV's dX
-    ATP_CHECK(sync_events(4 + 2 * (size_t)chunks, &ev));
-    ATP_CHECK(S.begin(ev[0]));
+    // [0..2] the streams'  [3] d_attn reduced  [4] QKV dX done, then the chunk
+    // events of out-proj's dX and of QKV's dX
+    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
+    ATP_CHECK(S.begin(ev));
+    hipEvent_t da_done = ev[3], dx_done = ev[4];
     auto make = [&](int L, const void* dY, int64_t lddy) {
         return [&, L, lddy](const void* A, void* C, int64_t ldc, bool b16, int epi, int64_t M) {
             return dyw_problem(P.g[L], kn, w->w[L], w->ldw[L], A, lddy, C, ldc, b16, epi, M);
@@ -1765,11 +1833,11 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     // on cs while those reductions drain
     ATP_CHECK(chained_linear(S, go.bwd_size, go.bwd_index, io->d_attn_partials, io->ldp_da, pb16,
                              io->d_o, io->ld_do, go.k_loc, atp::EPI_NONE, nullptr, nullptr,
-                             io->d_attn, io->ld_d_attn, T, chunks, ev + 4, ev[2],
+                             io->d_attn, io->ld_d_attn, T, chunks, ev + 5, &da_done,
                              make(1, io->d_o, io->ld_do)));
     ATP_CHECK(dweights(go, 1, io->attn, io->ld_attn, io->d_o, io->ld_do, xt_a, dyt_o, S.cs));
     // the core's backward reads the device's columns of the whole d_attn
-    HIP_CHECK(hipStreamWaitEvent(S.cs, ev[2], 0), "hipStreamWaitEvent");
+    if (da_done) HIP_CHECK(hipStreamWaitEvent(S.cs, da_done, 0), "hipStreamWaitEvent");
     if (T > 0) {
         atp::AttentionBwdProblem p;
         p.qkv = io->qkv;
@@ -1796,10 +1864,10 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     // QKV: dX chunks from the gathered d_qkv (reduced on ms into dx), dW, db
     ATP_CHECK(chained_linear(S, gq.bwd_size, gq.bwd_index, io->dx_partials, io->ldp_dx, pb16,
                              io->d_qkv, io->ld_dqkv, gq.k_loc, atp::EPI_NONE, nullptr, nullptr,
-                             io->dx, io->ld_dx, T, chunks, ev + 4 + chunks, ev[3],
+                             io->dx, io->ld_dx, T, chunks, ev + 5 + chunks, &dx_done,
                              make(0, io->d_qkv, io->ld_dqkv)));
     ATP_CHECK(dweights(gq, 0, io->x_loc, io->ldx, io->d_qkv, io->ld_dqkv, xt_x, dyt_q, S.cs));
-    return S.end(ev[1]);
+    return S.end();
 }
 
 void atp_profile_enable(int32_t on) {

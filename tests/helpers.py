@@ -163,7 +163,8 @@ def run_block_fwd(inp, chunks, compute=None, comm=None, same_stream=False, works
     return out
 
 
-def run_block_bwd(inp, chunks, h_act=None, pre=None, same_stream=False, workspace=False):
+def run_block_bwd(inp, chunks, h_act=None, pre=None, same_stream=False, workspace=False,
+                  comm=None):
     T, G, m = inp["T"], inp["G"], inp["m"]
     dev_ = inp["x"].device
     h_act = inp["hs"] if h_act is None else h_act
@@ -182,7 +183,7 @@ def run_block_bwd(inp, chunks, h_act=None, pre=None, same_stream=False, workspac
                               device=dev_) for g in G],
                db=[torch.full((g.n_loc,), float("nan"), device=dev_) for g in G])
     cs = torch.cuda.current_stream()
-    ms = cs if same_stream else torch.cuda.Stream()
+    ms = cs if same_stream else (comm or torch.cuda.Stream())
     atp.atp_block_bwd(m, block_mode_code(inp["mode"]), T, inp["h"], chunks, inp["w"], inp["b"],
                       inp["x"], inp["a"], h_act, pre, inp["dz"], inp["dqkv"], inp["do"], tabs,
                       out["dh_pre"], out["dx_qkv"], out["dx_fc1"], out["d_attn"], out["dw"],

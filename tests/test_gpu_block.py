@@ -400,3 +400,40 @@ def test_concurrent_calls_from_two_threads():
         for out in results[i]:
             for key in ("qkv", "o", "h", "pre", "z"):
                 assert torch.equal(_bits(out[key]), _bits(ref[i][key])), (i, key)
+
+
+@pytest.mark.parametrize("T,h,chunks", [(256, 512, 2), (130, 512, 1), (4096, 2048, 2)])
+def test_reductions_keep_their_place_on_the_comm_stream(T, h, chunks):
+    """Peers' partials written on comm_stream just before the call are in the
+    sums, and work queued there after the call finds the outputs written,
+    whether the reductions ran on comm_stream (the large case) or, being
+    short, on compute_stream."""
+    print(f"comm stream order T={T} h={h}", flush=True)
+    inp = make_block_inputs("col", (2, 2), (1, 0), T, h, 0.02, seed=71, on_device=True, bwd=True)
+    ref = run_block_fwd(inp, chunks, same_stream=True)
+    rbwd = run_block_bwd(inp, chunks, same_stream=True)
+    torch.cuda.synchronize()
+    late = {k: [[p.clone() for p in ps] for ps in inp[k]] for k in ("peers", "dx_peers")}
+    big = torch.empty(64 << 20, device=DEV)
+    for fwd, want, keys in ((True, ref, ("qkv", "o", "h", "z")),
+                            (False, rbwd, ("dh_pre", "dx_qkv", "dx_fc1", "d_attn"))):
+        name = "peers" if fwd else "dx_peers"
+        for ps in inp[name]:
+            for p in ps:
+                p.fill_(float("nan"))
+        torch.cuda.synchronize()
+        comm = torch.cuda.Stream()
+        with torch.cuda.stream(comm):
+            big.fill_(1.0)                         # keeps the stream busy first
+            for ps, vs in zip(inp[name], late[name]):
+                for p, v in zip(ps, vs):
+                    p.copy_(v)
+        if fwd:
+            out = run_block_fwd(inp, chunks, comm=comm)
+        else:
+            out = run_block_bwd(inp, chunks, comm=comm)
+        with torch.cuda.stream(comm):
+            seen = {k: out[k].clone() for k in keys}
+        torch.cuda.synchronize()
+        for k in keys:
+            assert torch.equal(_bits(seen[k]), _bits(want[k])), (T, k)
