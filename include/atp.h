@@ -335,7 +335,10 @@ atp_status atp_transpose_bf16(int64_t rows, int64_t cols, const void* src, int64
 /* One device's forward share of the layer (Sec. 3.2.1) with chunk-based
  * overlapping (Sec. 4.1).  Each linear's GEMM runs chunk by chunk; each
  * chunk's reduction runs on comm_stream as soon as that chunk's partial is
- * written; fc2's chunk c waits for fc1's reduced chunk c.  A group of one
+ * written (one that moves at most 8 MB is too short to hide anything and runs
+ * on compute_stream, except under graph capture: still after comm_stream's
+ * earlier work, and comm_stream is ordered after it when the call returns);
+ * fc2's chunk c waits for fc1's reduced chunk c.  A group of one
  * needs no reduction: its bias (and GeLU) are applied in the GEMM epilogue
  * and it runs as one launch.  The GEMMs are issued on compute_stream in the
  * order out-proj, fc1, then QKV and fc2 (the one whose reductions read fewer
@@ -379,8 +382,8 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
  * (fc1 waits for it), QKV's and out-proj's dX, fc1's dX, then the four dW
  * largest first, so the dX reductions overlap the later GEMMs.
  * workspace: when ws_bytes is at least the backward's need and tokens % 8
- * == 0 (atp_block_workspace_path), X^T and dY^T are written there and every
- * dW runs from them, weights stored [n_loc][k_loc] are copied there in
+ * == 0 (atp_block_workspace_path), X^T and dY^T are written there and dW
+ * runs from them where that is faster than reading X and dY as given, weights stored [n_loc][k_loc] are copied there in
  * [k_loc][n_loc] order for the dX products, and the chunked dX products are
  * split over their contraction as in atp_block_fwd; otherwise every product
  * reads its operands as stored.  The paths give the same bits except where
@@ -506,9 +509,10 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
  * workspace / ws_bytes: optional, caller-owned device memory (256-byte
  * aligned).  A workspace of atp_block_workspace_bytes() bytes for the same
  * mesh, mode, tokens, h and weight layout (or larger), with tokens a
- * multiple of 8, runs both dW products from transposed copies of X and dY
- * kept there (both operands contiguous along the tokens) and forms db from
- * the dY transpose; otherwise dW reads X and dY as given.  Both paths give
+ * multiple of 8, runs the dW products from transposed copies of X and dY
+ * kept there (both operands contiguous along the tokens), with db from the
+ * dY transpose, where that is the faster way; otherwise dW reads X and dY as
+ * given.  Both paths give
  * the same bits.  The workspace is scratch: nothing in it is read before
  * the call writes it.
  * Without such a workspace (or with tokens not a multiple of 8) the call

@@ -1173,6 +1173,23 @@ atp_status weight_grads_ws(const atp_shard& g, bool kn, const void* X, int64_t l
     return run_gemm(p, s);
 }
 
+// True when dW of a linear reads X and dY as given (TN, db by the column sum)
+// although the workspace has places for X^T and dY^T: the TN product's extra
+// time is less than the copies'.  Modelled: the products by their tiles, a
+// copy 3.5 us and its bytes at 4.8 TB/s (8192 x 6144 41 us), the column sum 4 us
+// and dY at 5 TB/s (h = 4096 layer backward 1577 -> 1561 us, attention block
+// forward and backward 993 -> 978).  The wide layer's dW (256 x 256 tiles, 16%
+// slower TN) run from copies.  Both give the same bits.
+bool dw_direct(const atp_shard& g, bool kn, int64_t T, bool copy_x, bool db) {
+    const int64_t M = kn ? g.k_loc : g.n_loc, N = kn ? g.n_loc : g.k_loc;
+    auto copy = [&](int64_t cols) { return 3.5 + 4.0 * (double)T * (double)cols / 4.8e6; };
+    const double tn = atp::gemm_model_us(atp::LAYOUT_TN, M, N, T) +
+                      (db ? 4.0 + 2.0 * (double)T * (double)g.n_loc / 5e6 : 0.0);
+    const double nt = atp::gemm_model_us(atp::LAYOUT_NT, M, N, T) + copy(g.n_loc) +
+                      (copy_x ? copy(g.k_loc) : 0.0) + (db ? 3.0 : 0.0);
+    return tn < nt;
+}
+
 // Bytes the attention block's backward carves from a workspace: X^T of x
 // and of the gathered block, dY^T of d_qkv and d_o, db's column partials
 // (a subset of the block backward's pieces, so ws_bwd_bytes covers it).
@@ -1597,7 +1614,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         const atp_shard& g = P.g[L];
         if (L == 2) ATP_CHECK(wait_dpre(chunks - 1));
         const int xi = xsrc[L];
-        if (!ws)
+        if (!ws || dw_direct(g, kn, tokens, !xt_done[xi], io->db[L] != nullptr))
             return weight_grads(g, kn, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L], w->ldw[L],
                                 io->db[L], tokens, S.cs);
         // X^T once per source (x serves QKV and fc1), dY^T, then the NT
@@ -1811,7 +1828,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     }
     auto dweights = [&](const atp_shard& g, int L, const void* X, int64_t ldx, const void* dY,
                         int64_t lddy, uint16_t* xt, uint16_t* dyt, hipStream_t s) {
-        if (ws)
+        if (ws && !dw_direct(g, kn, T, true, io->db[L] != nullptr))
             return weight_grads_ws(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T,
                                    xt, dyt, colpart, s);
         return weight_grads(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T, s);

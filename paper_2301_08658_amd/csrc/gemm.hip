@@ -1049,6 +1049,12 @@ const char* gemm_kernel_name(const GemmProblem& p) {
     return p.splits > 1 ? split[l] : names[l][pick_tile(p)];
 }
 
+double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K) {
+    double us = 0.0;
+    pick_tile(layout, M, N, K, 1, false, &us);
+    return us;
+}
+
 double nn_extra_us(int64_t M, int64_t N, int64_t K) {
     double us = 0.0;
     const TileCfg c = pick_tile(LAYOUT_NN, M, N, K, 1, false, &us);

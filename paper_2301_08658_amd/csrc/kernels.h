@@ -56,6 +56,8 @@ constexpr int kMaxSplits = 16;
 constexpr int64_t kMaxSplitTiles = 512;
 int nt_split_limit(int64_t M, int64_t N, int64_t K);
 int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit);
+// Modelled time (us) of an unsplit product on the tiles it would take.
+double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K);
 // Modelled time (us) that an unsplit product loses by reading B along its rows
 // (NN) instead of along k (NT): none on 256 x 256 tiles, about a tenth on the
 // smaller ones (1003 x 2056 x 1608 and 2048 x 6144 x 1024 measured).
