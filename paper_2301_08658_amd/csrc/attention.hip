@@ -7,7 +7,8 @@
 // 128, keys in steps of 64 (flash-attention style: running row maximum and
 // sum, the output rescaled as they grow).  Large grids: 128-row tiles, four
 // waves of two 16-row blocks.  Small grids: 64-row tiles, two groups of four
-// waves of 16 rows that split the tile's keys and merge at the end.
+// waves of 16 rows that split the tile's keys and merge at the end, fed by four
+// producer waves.
 //
 //   * S = Q K^T on v_mfma_f32_16x16x32_bf16: Q fragments stay in registers
 //     for the whole row tile; K fragments are ds_read_b128 from a [key][d]
@@ -196,6 +197,32 @@ struct TileDma2 {
     }
 };
 
+// The four producer waves of a kernel whose KG groups of consumer waves split
+// nkt key tiles (group 0 the first half, group 1 the rest): they copy every
+// group's K and V tile of step i into its buffer i & 1 before barrier i, at
+// which all consumers have finished step i - 1 (so step i - 2, the buffer's last
+// reader, since barrier i - 1).  Consumer waves then never stand at a copy
+// instruction (GPT-3 share forward 28 -> 25.4 us, one head of 4096 tokens 46.5 ->
+// 39.5).  Their barriers: one before the loop, one per step, one in the merge.
+template <int KG, class Cp>
+__device__ __forceinline__ void produce(const Cp& cp, const uint16_t* kbase,
+                                        const uint16_t* vbase, int64_t ld, int64_t tok0, int nkt,
+                                        int seq, uint16_t (&kv)[KG][2][2][BN * D], int wave) {
+    const int half = (nkt + 1) / 2;
+    for (int i = 0; i <= half; ++i) {
+        if (i < half) {
+#pragma unroll
+            for (int gr = 0; gr < KG; ++gr)
+                if (i < (gr == 0 ? half : nkt - half))
+                    cp.issue(kbase, ld, vbase, ld, tok0, (gr * half + i) * BN, seq,
+                             kv[gr][i & 1][0], kv[gr][i & 1][1], wave);
+            dma::wait_vmcnt<0>();
+        }
+        __syncthreads();
+    }
+    __syncthreads();
+}
+
 // RB row blocks of 16 queries per wave (query tile of 64 RB rows): every K
 // and V fragment read from LDS feeds RB MFMAs.  Block r of wave w holds rows
 // 64 r + 16 w .. + 15 of the tile.  KG groups of four waves split the tile's
@@ -204,13 +231,16 @@ struct TileDma2 {
 // output for the same rows, and group 1 hands them to group 0 through LDS at
 // the end, so no row loop is longer than half the causal row.
 template <int RB, int KG>
-__global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnArgs a) {
+__global__ __launch_bounds__(NTHR * KG + (KG > 1 ? NTHR : 0), KG > 1 ? 3 : 2)
+void attention_fwd_kernel(AttnArgs a) {
     constexpr int QT = 64 * RB;   // query rows per workgroup
+    constexpr bool PRODUCERS = KG > 1;
     __shared__ __attribute__((aligned(16))) uint16_t kv[KG][2][2][BN * D];   // [group][buf][K|V]
     __shared__ float mls[KG > 1 ? NWAVE * RB * 2 * 64 : 1];                // group 1's m, l
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int grp = wv / NWAVE, wave = wv % NWAVE;
+    const bool producer = PRODUCERS && wv >= KG * NWAVE;
+    const int grp = producer ? 0 : wv / NWAVE, wave = wv % NWAVE;
     // longest rows first: the last query tile of every (sequence, head) leads
     const int per = a.qtiles;
     const int bid = blockIdx.x;
@@ -220,6 +250,28 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnAr
     const int64_t tok0 = (int64_t)b * a.seq;
     const int64_t qc = a.col0 + (int64_t)hh * 3 * D, kc = qc + D, vc = qc + 2 * D;
 
+    // causal: keys up to the tile's last row inside the sequence; group 0
+    // takes key tiles [0, half), group 1 [half, nkt)
+    const int last = min(qt * QT + QT, a.seq) - 1;
+    const int nkt = last / BN + 1;
+    const int half = KG > 1 ? (nkt + 1) / 2 : nkt;
+    const int kt0 = grp == 0 ? 0 : half;
+    const int mine = grp == 0 ? half : nkt - half;   // <= half
+    uint16_t(*buf)[2][BN * D] = kv[grp];
+    TileDma2<true> cp;
+    cp.init(a.ldq, a.ldq, wave, lane);
+    const uint16_t* kbase = a.qkv + kc;
+    const uint16_t* vbase = a.qkv + vc;
+    if constexpr (PRODUCERS) {
+        if (producer) {
+            produce<KG>(cp, kbase, vbase, a.ldq, tok0, nkt, a.seq, kv, wave);
+            return;
+        }
+    } else {
+        if (mine > 0)
+            cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, kt0 * BN, a.seq, buf[0][0], buf[0][1], wave);
+        dma::wait_vmcnt<0>();
+    }
     // Q fragments: row mrow[r], d = 32 ks + 8 (lane / 16) + 0..7
     int mrow[RB];
     bf16x8 qf[RB][4];
@@ -246,21 +298,6 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnAr
         lrun[r] = 0.f;
     }
 
-    // causal: keys up to the tile's last row inside the sequence; group 0
-    // takes key tiles [0, half), group 1 [half, nkt)
-    const int last = min(qt * QT + QT, a.seq) - 1;
-    const int nkt = last / BN + 1;
-    const int half = KG > 1 ? (nkt + 1) / 2 : nkt;
-    const int kt0 = grp == 0 ? 0 : half;
-    const int mine = grp == 0 ? half : nkt - half;   // <= half
-    uint16_t(*buf)[2][BN * D] = kv[grp];
-    TileDma2<true> cp;
-    cp.init(a.ldq, a.ldq, wave, lane);
-    const uint16_t* kbase = a.qkv + kc;
-    const uint16_t* vbase = a.qkv + vc;
-    if (mine > 0)
-        cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, kt0 * BN, a.seq, buf[0][0], buf[0][1], wave);
-    dma::wait_vmcnt<0>();
     __syncthreads();
     const int g = lane >> 4, l16 = lane & 15;
     // K fragment offsets (key row 16 j + l16: j adds 16 rows), V read offsets
@@ -277,7 +314,7 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_fwd_kernel(AttnAr
             const uint16_t* ks_ = buf[i & 1][0];
             const uint16_t* vs_ = buf[i & 1][1];
             // the other buffer was last read in step i - 1, before its barrier
-            const bool more = i + 1 < mine;
+            const bool more = !PRODUCERS && i + 1 < mine;
             const auto next = cp.rounds(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
                                         buf[(i + 1) & 1][0], buf[(i + 1) & 1][1]);
 
@@ -650,12 +687,15 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dkv_kernel(AttnBw
 // tile's key tiles (group 0 the first half, group 1 the rest, with the
 // diagonal); group 1 adds its sums into group 0's through LDS at the end.
 template <int RB, int KG>
-__global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dq_kernel(AttnBwdArgs a) {
+__global__ __launch_bounds__(NTHR * KG + (KG > 1 ? NTHR : 0), KG > 1 ? 3 : 2)
+void attention_dq_kernel(AttnBwdArgs a) {
     constexpr int QT = 64 * RB;
+    constexpr bool PRODUCERS = KG > 1;
     __shared__ __attribute__((aligned(16))) uint16_t kv[KG][2][2][BN * D];   // [grp][buf][K|V]
     const int lane = threadIdx.x & 63, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int grp = wv / NWAVE, wave = wv % NWAVE;
+    const bool producer = PRODUCERS && wv >= KG * NWAVE;
+    const int grp = producer ? 0 : wv / NWAVE, wave = wv % NWAVE;
     const int bhn = a.batch * a.heads;
     const int qt = a.tiles - 1 - blockIdx.x / bhn;   // long loops first
     const int bh = blockIdx.x % bhn;
@@ -663,6 +703,28 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dq_kernel(AttnBwd
     const int64_t tok0 = (int64_t)b * a.seq, T = (int64_t)a.batch * a.seq;
     const int64_t qc = a.col0 + (int64_t)hh * 3 * D;
 
+    const uint16_t* kbase = a.qkv + qc + D;
+    const uint16_t* vbase = a.qkv + qc + 2 * D;
+    // key tiles up to the tile's last row inside the sequence: group 0 the
+    // first half, group 1 the rest
+    const int last = min(qt * QT + QT, a.seq) - 1;
+    const int nk = last / BN + 1;
+    const int half = KG > 1 ? (nk + 1) / 2 : nk;
+    const int k0 = grp == 0 ? 0 : half;
+    const int mine = grp == 0 ? half : nk - half;   // <= half
+    uint16_t(*kb)[2][BN * D] = kv[grp];
+    TileDma2<false> cp;
+    cp.init(a.ldq, a.ldq, wave, lane);
+    if constexpr (PRODUCERS) {
+        if (producer) {
+            produce<KG>(cp, kbase, vbase, a.ldq, tok0, nk, a.seq, kv, wave);
+            return;
+        }
+    } else {
+        if (mine > 0)
+            cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, k0 * BN, a.seq, kb[0][0], kb[0][1], wave);
+        dma::wait_vmcnt<0>();
+    }
     int qabs[RB];
     bf16x8 qf[RB][4], of[RB][4];
     float l2[RB], dl[RB];
@@ -713,28 +775,13 @@ __global__ __launch_bounds__(NTHR * KG, 2 / KG) void attention_dq_kernel(AttnBwd
 
     int boff[4], toff[8];
     offsets(lane, boff, toff);
-    const uint16_t* kbase = a.qkv + qc + D;
-    const uint16_t* vbase = a.qkv + qc + 2 * D;
-    // key tiles up to the tile's last row inside the sequence: group 0 the
-    // first half, group 1 the rest
-    const int last = min(qt * QT + QT, a.seq) - 1;
-    const int nk = last / BN + 1;
-    const int half = KG > 1 ? (nk + 1) / 2 : nk;
-    const int k0 = grp == 0 ? 0 : half;
-    const int mine = grp == 0 ? half : nk - half;   // <= half
-    uint16_t(*kb)[2][BN * D] = kv[grp];
-    TileDma2<false> cp;
-    cp.init(a.ldq, a.ldq, wave, lane);
-    if (mine > 0)
-        cp.issue(kbase, a.ldq, vbase, a.ldq, tok0, k0 * BN, a.seq, kb[0][0], kb[0][1], wave);
-    dma::wait_vmcnt<0>();
     __syncthreads();
     for (int i = 0; i < half; ++i) {
         if (i < mine) {
             const int kt = k0 + i;
             const uint16_t* ks_ = kb[i & 1][0];
             const uint16_t* vs_ = kb[i & 1][1];
-            const bool more = i + 1 < mine;
+            const bool more = !PRODUCERS && i + 1 < mine;
             const auto next = cp.rounds(kbase, a.ldq, vbase, a.ldq, tok0, (kt + 1) * BN, a.seq,
                                         kb[(i + 1) & 1][0], kb[(i + 1) & 1][1]);
             // S and dP: lane holds (query = qabs[r], key = 16 j + 4 g + e); a
@@ -867,11 +914,11 @@ hipError_t launch_attention_bwd(const AttentionBwdProblem& p, hipStream_t s) {
     // the dQ kernel first: it forms delta for its query rows and stores it
     // for the dK/dV kernel.  Small grids split each workgroup's loop over two
     // groups of four waves (one workgroup per CU), so the longest loops take
-    // half as many steps; dQ takes 128-row query tiles (two row blocks per
-    // wave) when they still give every CU two workgroups.
+    // half as many steps; else dQ takes 128-row query tiles (two row blocks per
+    // wave).
     const bool split = grid < kBwdSplitGrid;
     if (split) {
-        hipLaunchKernelGGL((attention_dq_kernel<1, 2>), dim3((unsigned)grid), dim3(2 * NTHR), 0,
+        hipLaunchKernelGGL((attention_dq_kernel<1, 2>), dim3((unsigned)grid), dim3(3 * NTHR), 0,
                            s, a);
         hipLaunchKernelGGL((attention_dkv_kernel<2>), dim3((unsigned)grid), dim3(2 * NTHR), 0, s,
                            a);
@@ -879,12 +926,8 @@ hipError_t launch_attention_bwd(const AttentionBwdProblem& p, hipStream_t s) {
     }
     AttnBwdArgs a2 = a;
     a2.tiles = (int)((p.seq + 127) / 128);
-    const int64_t grid2 = (int64_t)a2.tiles * a.batch * a.heads;
-    if (grid2 >= kFwdWideGrid)
-        hipLaunchKernelGGL((attention_dq_kernel<2, 1>), dim3((unsigned)grid2), dim3(NTHR), 0, s,
-                           a2);
-    else
-        hipLaunchKernelGGL((attention_dq_kernel<1, 1>), dim3((unsigned)grid), dim3(NTHR), 0, s, a);
+    const int64_t grid2 = (int64_t)a2.tiles * a.batch * a.heads;   // >= grid / 2: two per CU
+    hipLaunchKernelGGL((attention_dq_kernel<2, 1>), dim3((unsigned)grid2), dim3(NTHR), 0, s, a2);
     hipLaunchKernelGGL((attention_dkv_kernel<1>), dim3((unsigned)grid), dim3(NTHR), 0, s, a);
     return hipGetLastError();
 }
@@ -919,7 +962,7 @@ hipError_t launch_attention_fwd(const AttentionProblem& p, hipStream_t s) {
         hipLaunchKernelGGL((attention_fwd_kernel<2, 1>), dim3((unsigned)grid), dim3(NTHR), 0, s,
                            a);
     else
-        hipLaunchKernelGGL((attention_fwd_kernel<1, 2>), dim3((unsigned)grid), dim3(2 * NTHR), 0,
+        hipLaunchKernelGGL((attention_fwd_kernel<1, 2>), dim3((unsigned)grid), dim3(3 * NTHR), 0,
                            s, a);
     return hipGetLastError();
 }
