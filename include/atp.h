@@ -114,7 +114,8 @@ atp_status atp_shard_geometry(const atp_mesh* mesh, int32_t mode, int64_t k, int
  * be NONE, BIAS or BIAS_GELU and y f32 or bf16; bias_loc bf16 [n_loc]
  * (the block n_off..), preact (nullable, bf16, ld ldy) receives s + b for
  * BIAS_GELU.  chunk_done (nullable) holds `chunks` caller-created events;
- * event c is recorded on `stream` once chunk c's rows of y are written. */
+ * event c is recorded on `stream` once chunk c's rows of y are written
+ * (chunks with no event between them run as one launch). */
 atp_status atp_shard_linear_fwd(const atp_mesh* mesh, int32_t mode, int64_t tokens,
                                 int64_t k, int64_t n, int32_t chunks,
                                 const void* x_loc, int64_t ldx,
@@ -383,10 +384,10 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
  * largest first, so the dX reductions overlap the later GEMMs.
  * workspace: when ws_bytes is at least the backward's need and tokens % 8
  * == 0 (atp_block_workspace_path), X^T and dY^T are written there and dW
- * runs from them where that is faster than reading X and dY as given, weights stored [n_loc][k_loc] are copied there in
- * [k_loc][n_loc] order for the dX products, and the chunked dX products are
- * split over their contraction as in atp_block_fwd; otherwise every product
- * reads its operands as stored.  The paths give the same bits except where
+ * runs from them where that is faster than reading X and dY as given, weights
+ * stored [n_loc][k_loc] are copied there in [k_loc][n_loc] order for the dX
+ * products, and the chunked dX products are split over their contraction as
+ * in atp_block_fwd; otherwise every product reads its operands as stored.  The paths give the same bits except where
  * a product splits (as in atp_block_fwd).  On return compute_stream is
  * ordered after all work.  Graph capture and threads as atp_block_fwd. */
 atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t tokens, int64_t h,
@@ -512,8 +513,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
  * multiple of 8, runs the dW products from transposed copies of X and dY
  * kept there (both operands contiguous along the tokens), with db from the
  * dY transpose, where that is the faster way; otherwise dW reads X and dY as
- * given.  Both paths give
- * the same bits.  The workspace is scratch: nothing in it is read before
+ * given.  Both paths give the same bits.  The workspace is scratch: nothing in it is read before
  * the call writes it.
  * Without such a workspace (or with tokens not a multiple of 8) the call
  * refuses a compute_stream under HIP graph capture.  Errors as

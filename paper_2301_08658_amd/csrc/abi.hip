@@ -739,6 +739,20 @@ atp_status atp_shard_geometry(const atp_mesh* mesh, int32_t mode, int64_t k, int
     return geometry(mesh, mode, k, n, out);
 }
 
+extern "C++" {
+namespace {
+// Chunks of a single-stream call are apart only where an event stands between
+// them: the last of the chunks from c on that one launch can cover, up to the
+// next that `done` marks.  One launch fills the chip better than several
+// (2048 x 1024 x 4096 dX in 2 chunks: two products of 19 us, one of 24; the bits
+// do not depend on the rows of a launch).
+int32_t last_of_run(void* const* done, int32_t c, int32_t chunks) {
+    while (c < chunks - 1 && !(done && done[c])) ++c;
+    return c;
+}
+}  // namespace
+}  // extern "C++"
+
 atp_status atp_shard_linear_fwd(const atp_mesh* mesh, int32_t mode, int64_t tokens, int64_t k,
                                 int64_t n, int32_t chunks, const void* x_loc, int64_t ldx,
                                 const void* w_loc, int64_t ldw, const void* bias_loc,
@@ -767,11 +781,13 @@ atp_status atp_shard_linear_fwd(const atp_mesh* mesh, int32_t mode, int64_t toke
     const int64_t mc = tokens / chunks;
     const bool b16 = (y_dtype == ATP_BF16);
     const size_t esz = b16 ? 2 : 4;
-    for (int32_t c = 0; c < chunks; ++c) {
-        const int64_t r0 = (int64_t)c * mc;
+    for (int32_t c0 = 0, c = 0; c0 < chunks; c0 = c + 1) {
+        c = last_of_run(chunk_done, c0, chunks);
+        const int64_t r0 = (int64_t)c0 * mc;
         atp::GemmProblem p = gemm_problem(
             atp::LAYOUT_NN, static_cast<const uint16_t*>(x_loc) + r0 * ldx, ldx, w_loc, ldw,
-            static_cast<char*>(y) + r0 * ldy * esz, ldy, b16, epi, mc, g.n_loc, g.k_loc);
+            static_cast<char*>(y) + r0 * ldy * esz, ldy, b16, epi, (c - c0 + 1) * mc, g.n_loc,
+            g.k_loc);
         p.bias = bias_loc;
         if (preact) p.pre_out = static_cast<uint16_t*>(preact) + r0 * ldy;
         ATP_CHECK(run_gemm(p, s));
@@ -812,12 +828,14 @@ atp_status chunked_reduce(int32_t red_size, int64_t tokens, int64_t n_loc, int32
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mc = tokens / chunks;
-    for (int32_t c = 0; c < chunks; ++c) {
+    for (int32_t c = 0, n = 1; c < chunks; c += n) {
         if (chunk_ready && chunk_ready[c])
             HIP_CHECK(hipStreamWaitEvent(s, static_cast<hipEvent_t>(chunk_ready[c]), 0),
                       "hipStreamWaitEvent");
-        atp::ReduceProblem p = reduce_problem(red_size, partials, ldp, (int64_t)c * mc, mc, n_loc,
-                                              epi, bias_loc, preact_in, out, ldo,
+        // with the chunks after it that wait for nothing, one launch
+        for (n = 1; c + n < chunks && !(chunk_ready && chunk_ready[c + n]); ++n) {}
+        atp::ReduceProblem p = reduce_problem(red_size, partials, ldp, (int64_t)c * mc, n * mc,
+                                              n_loc, epi, bias_loc, preact_in, out, ldo,
                                               out_dtype == ATP_BF16, preact_out, parts_bf16);
         ATP_CHECK(run_reduce(p, s));
     }
@@ -909,13 +927,14 @@ atp_status atp_shard_linear_bwd(const atp_mesh* mesh, int32_t mode, int64_t toke
     if (db) ATP_CHECK(check_vec(db, "db"));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t mc = tokens / chunks;
-    for (int32_t c = 0; c < chunks; ++c) {
-        const int64_t r0 = (int64_t)c * mc;
+    for (int32_t c0 = 0, c = 0; c0 < chunks; c0 = c + 1) {
+        c = last_of_run(dx_chunk_done, c0, chunks);
+        const int64_t r0 = (int64_t)c0 * mc;
         // dX = dY W^T : B(k=n', col=k') = W[k'][n'], contiguous along the contraction
         atp::GemmProblem p = gemm_problem(atp::LAYOUT_NT,
                                           static_cast<const uint16_t*>(dy) + r0 * lddy, lddy,
                                           w_loc, ldw, dx_partial + r0 * lddx, lddx, false,
-                                          atp::EPI_NONE, mc, g.k_loc, g.n_loc);
+                                          atp::EPI_NONE, (c - c0 + 1) * mc, g.k_loc, g.n_loc);
         ATP_CHECK(run_gemm(p, s));
         if (dx_chunk_done && dx_chunk_done[c])
             HIP_CHECK(hipEventRecord(static_cast<hipEvent_t>(dx_chunk_done[c]), s),

@@ -180,3 +180,33 @@ def test_bias_gradient_rounds_and_widths_integer_bit_exact(T, N):
                              torch.empty((T, 8), device=DEV), torch.empty((8, N), device=DEV), db)
     _sync()
     assert torch.equal(db.double(), dy.double().sum(0))
+
+
+@pytest.mark.parametrize("marked", [(), (1,), (0, 2), (0, 1, 2, 3)])
+def test_chunks_run_together_up_to_the_next_event(marked):
+    """Chunks with no event between them run as one launch: the products, the
+    reduction and every event's rows are those of single chunks."""
+    T, K, N, chunks = 264, 96, 136, 4
+    m = atp.mesh(1, 1)
+    print(f"events at {marked}", flush=True)
+    ev = [atp.HipEvent() if c in marked else None for c in range(chunks)]
+    x, w = S.randint_bf16((T, K), 10, 1).to(DEV), S.randint_bf16((K, N), 10, 2).to(DEV)
+    dy = S.randint_bf16((T, N), 10, 3).to(DEV)
+    y, dx = torch.full((T, N), float("nan"), device=DEV), torch.full((T, K), float("nan"), device=DEV)
+    dw, z = torch.empty((K, N), device=DEV), torch.full((T, N), float("nan"), device=DEV)
+    other = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    atp.atp_shard_linear_fwd(m, 0, T, K, N, chunks, x, w, None, atp.ATP_EPI_NONE, y, chunk_done=ev)
+    # the reduction on another stream waits for the same events, then for all
+    if marked and marked[-1] != chunks - 1 or not marked:
+        torch.cuda.synchronize()
+    atp.atp_chunked_partial_reduce(2, T, N, chunks, [y, y], None, atp.ATP_EPI_NONE, z,
+                                   stream=other, chunk_ready=ev)
+    atp.atp_shard_linear_bwd(m, 0, T, K, N, chunks, x, w, dy, dx, dw, None, dx_chunk_done=ev)
+    for e in ev:
+        if e is not None:
+            e.synchronize()
+    _sync()
+    ref = torch.matmul(x.double(), w.double())
+    assert torch.equal(y.double(), ref) and torch.equal(z.double(), 2 * ref)
+    assert torch.equal(dx.double(), torch.matmul(dy.double(), w.double().t()))
