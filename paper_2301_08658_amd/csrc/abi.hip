@@ -1308,7 +1308,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     // With a large enough workspace every forward product runs with both
     // operands contiguous along k (the layout the GEMM kernel streams
     // fastest; weights stored [k][n] are first copied there as W^T, unless
-    // the linear's products stream NN as fast: fwd_reads_w), and chunk
+    // its NN products all run on the 256 x 256 tiles: fwd_reads_w), and chunk
     // products with too few tiles to fill the chip are split over k into
     // slabs there.  The direct path never runs under graph capture.
     const bool ws = workspace && takes_ws_path(P, tokens, w->layout, ws_bytes, 0);

@@ -5,8 +5,8 @@
 // (Sec. 3.2 forward Y = X W; Sec. 4.2 backward dX = dY W^T, dW = X^T dY) in
 // each operand layout: an operand is either contiguous along k (X, dY, and
 // W in dX; the transposed copies W^T, X^T, dY^T of the workspace path) or
-// contiguous along its rows (W in the forward, X and dY in dW without a
-// workspace).  The kernels are described below; every layout and tile sums an
+// contiguous along its rows (W in the forward, X and dY in a dW product that
+// reads them as given).  The kernels are described below; every layout and tile sums an
 // output element's products in the same order, so they give the same bits.
 //
 //   * Operands go global -> LDS with buffer_load_dwordx4 ... lds (no
