@@ -384,7 +384,8 @@ size_t slab_bytes(const BlockPlan& P, int64_t tokens, bool bwd, int nlin = 4) {
             const atp_shard& g = P.g[L];
             if ((bwd ? g.bwd_size : g.red_size) <= 1) continue;
             const int64_t N = bwd ? g.k_loc : g.n_loc, K = bwd ? g.n_loc : g.k_loc;
-            const int S = atp::nt_split_limit(mc, N, K);
+            int64_t ks = 0;
+            const int S = atp::nt_split_plan(mc, N, K, &ks);
             if (S > 1) most = std::max(most, (size_t)S * mc * N * 4);
         }
     }
@@ -403,8 +404,9 @@ bool fwd_may_copy_w(const BlockPlan& P, int L, int64_t tokens) {
     for (int c = 1; c <= ATP_MAX_CHUNKS; ++c) {
         if (tokens % c) continue;
         const int64_t mc = tokens / c;
+        int64_t ks = 0;
         if (g.red_size <= 1 ? !atp::nn_large_tiles(tokens, g.n_loc)
-                            : atp::nt_split_limit(mc, g.n_loc, g.k_loc) > 1 ||
+                            : atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) > 1 ||
                                   !atp::nn_large_tiles(mc, g.n_loc))
             return true;
     }
@@ -477,13 +479,17 @@ bool takes_ws_path(const BlockPlan& P, int64_t tokens, int32_t layout, size_t ws
 }
 
 // A partial product [M, N] over K (fp32, or bf16 when p.out_bf16): split
-// over K into `slab` when a slab is given and the plan says so, the splits'
-// fp32 slabs then summed in split order into C (rounded once to bf16 for a
-// bf16 partial).
-atp_status run_nt_partial(atp::GemmProblem p, float* slab, hipStream_t s) {
+// over K when a slab is given and the plan says so: the splits' fp32 sums are
+// added in split order and written to C (rounded once to bf16 for a bf16
+// partial), through the slab or in the tile (the same bits).
+atp_status run_nt_partial(atp::GemmProblem p, float* slab, hipStream_t s, bool lanes = false) {
     int64_t ks = 0;
     const int S = slab ? atp::nt_split_plan(p.M, p.N, p.K, &ks) : 1;
     if (S <= 1) return run_gemm(p, s);
+    if (atp::nt_plan_in_tile(p.M, p.N, p.K, lanes)) {
+        p.seg = ks;
+        return run_gemm(p, s);
+    }
     void* out = p.C;
     const int64_t ldo = p.ldc;
     const bool b16 = p.out_bf16;
@@ -1402,7 +1408,8 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     };
     // chunk c: the GEMM writes this device's partial rows, the comm stream
     // reduces the group's partials for those rows as soon as they are ready
-    auto chunk = [&](int L, int c, hipStream_t st) -> atp_status {
+    auto chunk = [&](int L, int c, bool two) -> atp_status {
+        hipStream_t st = two && (c & 1) ? lane2 : S.cs;
         const atp_shard& g = P.g[L];
         const int64_t r0 = (int64_t)c * mc;
         if (L == 3) ATP_CHECK(wait_h(c, st));
@@ -1410,7 +1417,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         atp::GemmProblem p = fwd_problem(L, static_cast<const uint16_t*>(A_in[L]) + r0 * lda_in[L],
                                          lda_in[L], row_ptr(own, r0, io->ldp[L], pb16),
                                          io->ldp[L], pb16, atp::EPI_NONE, mc);
-        ATP_CHECK(run_nt_partial(p, slab, st));
+        ATP_CHECK(run_nt_partial(p, slab, st, two));
         hipStream_t rs = nullptr;
         ATP_CHECK(S.reduction(inl[L], st, ev_gemm[L * chunks + c], &rs));
         atp::ReduceProblem r = reduce_problem(
@@ -1432,13 +1439,14 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         ATP_CHECK(need_wt(L));
         int64_t ks = 0;
         const bool two = lane2 && !inl[L] &&
-                         (!slab || atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) <= 1);
+                         (!slab || atp::nt_split_plan(mc, g.n_loc, g.k_loc, &ks) <= 1 ||
+                          atp::nt_plan_in_tile(mc, g.n_loc, g.k_loc, true));
         if (two) {
             HIP_CHECK(hipEventRecord(ev[3], S.cs), "hipEventRecord");
             HIP_CHECK(hipStreamWaitEvent(lane2, ev[3], 0), "hipStreamWaitEvent");
             lane2_used = true;
         }
-        for (int c = 0; c < chunks; ++c) ATP_CHECK(chunk(L, c, two && (c & 1) ? lane2 : S.cs));
+        for (int c = 0; c < chunks; ++c) ATP_CHECK(chunk(L, c, two));
         return ATP_OK;
     };
     // out-proj first (its reductions start at once), then fc1; of QKV and fc2

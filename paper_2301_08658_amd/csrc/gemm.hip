@@ -68,6 +68,7 @@ struct KArgs {
     // and writes C + s*c_split (an fp32 slab per split); splits == 1: plain
     int splits;
     int64_t ksplit, c_split;
+    int seg_steps;   // K steps of a segment (kernels with SEG)
     // fused peer sum (nparts > 1): the group's partials summed in group
     // order, the tile's own accumulators at position own
     int nparts, own;
@@ -679,6 +680,12 @@ __global__ __launch_bounds__(nt::NT, 1) void gemm_nt_kernel(KArgs a) {
 //     CUs without one.
 // Copies, LDS layouts, fragments and the order of an element's products are
 // those of the large tiles, so every configuration gives the same bits.
+//
+// With SEG a tile forms the sums of a split-K plan itself: each segment of
+// seg_steps K steps accumulates from zero and is added to the segments before
+// it, which gives the bits of the splits' slabs summed in split order without
+// writing and reading them.  The second set of accumulators fits the tiles up to
+// 128 x 128 (256 x 128 has 164 of its 168 registers in use without it).
 // ---------------------------------------------------------------------------
 namespace st {
 
@@ -710,7 +717,7 @@ using Tile64 = Cfg<64, 64, 2, 2, 4, 2>;          // 64 KB, waves of 32 x 32
 
 }  // namespace st
 
-template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16>
+template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16, bool SEG = false>
 __global__ __launch_bounds__(C::NT, C::MINW) void gemm_small_kernel(KArgs a) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NW = C::NW, S = C::STAGES, PW = C::PW;
     constexpr int FM = C::FM, FN = C::FN;
@@ -769,6 +776,21 @@ __global__ __launch_bounds__(C::NT, C::MINW) void gemm_small_kernel(KArgs a) {
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 sum[SEG ? FM : 1][SEG ? FN : 1];   // the segments before acc's
+    if constexpr (SEG) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    auto add_segment = [&]() {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sum[i][j][e] += acc[i][j][e];
+    };
     bf16x8 fa[2][FM], fb[2][FN];
     auto read = [&](int p, int ks) {
         const uint16_t* sa = slot(p);
@@ -801,7 +823,23 @@ __global__ __launch_bounds__(C::NT, C::MINW) void gemm_small_kernel(KArgs a) {
                 __builtin_amdgcn_sched_barrier(0);
             }
             mul(1);
+            if constexpr (SEG) {
+                if ((p + 1) % a.seg_steps == 0 && p + 1 < nk) {
+                    add_segment();
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
         }
+    }
+    if constexpr (SEG) {
+        add_segment();
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[i][j] = sum[i][j];
     }
 
     // Epilogue: the fragment layout of the large tiles
@@ -840,6 +878,7 @@ KArgs kargs(const GemmProblem& p, int bm, int bn) {
     a.splits = p.splits > 1 ? p.splits : 1;
     a.ksplit = a.splits > 1 ? p.ksplit : p.K;
     a.c_split = p.c_split;
+    a.seg_steps = (int)(p.seg / 64);
     a.nparts = p.nparts > 1 ? p.nparts : 1;
     a.own = p.own;
     for (int j = 0; j < kMaxFusedParts; ++j) a.peers[j] = p.peers[j];
@@ -916,26 +955,43 @@ TileCfg pick_tile(int layout, int64_t M, int64_t N, int64_t K, int S, bool allow
     return best;
 }
 
+// The same among the tiles whose kernels form a split plan's sums themselves.
+TileCfg pick_seg_tile(int64_t M, int64_t N, int64_t K, double* us = nullptr) {
+    TileCfg best = T_128;
+    double least = tile_cost(LAYOUT_NT, T_128, M, N, K, 1);
+    for (TileCfg c : {T_64x128, T_64}) {
+        const double u = tile_cost(LAYOUT_NT, c, M, N, K, 1);
+        if (u < least) {
+            best = c;
+            least = u;
+        }
+    }
+    if (us) *us = least;
+    return best;
+}
+
 TileCfg pick_tile(const GemmProblem& p) {
+    if (p.seg > 0) return pick_seg_tile(p.M, p.N, p.K);
     return pick_tile(p.layout, p.M, p.N, p.splits > 1 ? p.ksplit : p.K,
                      p.splits > 1 ? p.splits : 1, rows_fit(320, p.ldb));
 }
 
-// Size bound of a product's split-K slabs (and whether it may split at all):
-// the S in 1..kMaxSplits that minimises a two-term cost, (rounds of 256
-// concurrent 256 x 160 tiles) x (k per split) x (flops per k per tile), plus the
-// fp32 slab traffic (each written once and read once) counted at equal per-CU
-// flop and chip byte rates (about 4 TFLOP/s per CU against about 4 TB/s),
-// with at most kMaxSplitTiles workgroups, at least 256 k in whole 64-k steps
-// per split and a gain of 15%.  The workspace is sized by it; the split a
-// product takes (pick_splits) never exceeds it.
-int split_limit(int64_t M, int64_t N, int64_t K) {
+// Split-K plan of an NT product written to fp32: the S in 1..kMaxSplits
+// that minimises a two-term cost, (rounds of 256 concurrent 256 x 160 tiles) x
+// (k per split) x (flops per k per tile), plus the fp32 slab traffic of the
+// splits (each written once and read once) counted at equal per-CU flop and
+// chip byte rates (about 4 TFLOP/s per CU against about 4 TB/s), with at most
+// kMaxSplitTiles workgroups, at least 256 k in whole 64-k steps per split and
+// a gain of 15%.  The plan fixes the order in which a partial's products are
+// summed, so it does not follow the tiles that the splits run on.
+int pick_splits(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
     constexpr int64_t kCUs = 256;
     const int64_t tiles = ((M + nt::BM - 1) / nt::BM) * ((N + 159) / 160);
     const double flops_per_k = 2.0 * nt::BM * 160;
     int best = 1;
     double best_cost = (double)((tiles + kCUs - 1) / kCUs) * K * flops_per_k;
     const double plain = best_cost;
+    *ksplit = K;
     for (int S = 2; S <= kMaxSplits; ++S) {
         const int64_t ks = ((K + S - 1) / S + 63) / 64 * 64;
         if (ks < 256 || (K + ks - 1) / ks != S || tiles * S > kMaxSplitTiles) continue;
@@ -944,36 +1000,12 @@ int split_limit(int64_t M, int64_t N, int64_t K) {
         if (cost < best_cost) {
             best = S;
             best_cost = cost;
-        }
-    }
-    return best > 1 && best_cost > 0.85 * plain ? 1 : best;
-}
-
-// Split-K plan of an NT product written to fp32: the S up to split_limit with
-// the least modelled time of its tiles plus their sum, taken when it gains 5%.
-// Slabs up to 16 MB are read back from the caches (10 TB/s); larger ones cost
-// their reads and the sum's write at 2.5 TB/s (2048 x 1024 in two splits: 8-13
-// us beside the other work of a step).
-int pick_splits(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
-    int best = 1;
-    *ksplit = K;
-    const int limit = split_limit(M, N, K);
-    if (limit <= 1) return 1;
-    double least = 0.0;
-    pick_tile(LAYOUT_NT, M, N, K, 1, false, &least);
-    least *= 0.95;
-    for (int S = 2; S <= limit; ++S) {
-        const int64_t ks = ((K + S - 1) / S + 63) / 64 * 64;
-        if (ks < 256 || (K + ks - 1) / ks != S) continue;
-        double us = 0.0;
-        pick_tile(LAYOUT_NT, M, N, ks, S, false, &us);
-        const double el = (double)M * (double)N;
-        us += 4.0 * S * el <= 16e6 ? 4.0 * S * el / 1e7 : 4.0 * (S + 1) * el / 2.5e6;
-        if (us < least) {
-            best = S;
-            least = us;
             *ksplit = ks;
         }
+    }
+    if (best > 1 && best_cost > 0.85 * plain) {
+        best = 1;
+        *ksplit = K;
     }
     return best;
 }
@@ -988,14 +1020,23 @@ hipError_t launch_pp_cfg(const GemmProblem& p, hipStream_t s) {
     return hipGetLastError();
 }
 
-template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16>
+template <class C, bool A_K, bool B_K, int EPI, bool OUT_BF16, bool SEG = false>
 hipError_t launch_small(const GemmProblem& p, hipStream_t s) {
     const KArgs a = kargs(p, C::BM, C::BN);
     const int grid = a.tiles_m * a.tiles_n * a.splits;
     if (grid == 0) return hipSuccess;
-    hipLaunchKernelGGL((gemm_small_kernel<C, A_K, B_K, EPI, OUT_BF16>), dim3(grid), dim3(C::NT), 0,
-                       s, a);
+    hipLaunchKernelGGL((gemm_small_kernel<C, A_K, B_K, EPI, OUT_BF16, SEG>), dim3(grid),
+                       dim3(C::NT), 0, s, a);
     return hipGetLastError();
+}
+
+template <bool OUT_BF16>
+hipError_t launch_seg(const GemmProblem& p, hipStream_t s) {
+    switch (pick_tile(p)) {
+    case T_128: return launch_small<st::Tile128, true, true, EPI_NONE, OUT_BF16, true>(p, s);
+    case T_64x128: return launch_small<st::Tile64x128, true, true, EPI_NONE, OUT_BF16, true>(p, s);
+    default: return launch_small<st::Tile64, true, true, EPI_NONE, OUT_BF16, true>(p, s);
+    }
 }
 
 // Operands contiguous along k (A_K / B_K) or along their rows.
@@ -1046,6 +1087,10 @@ const char* gemm_kernel_name(const GemmProblem& p) {
     static const char* const split[3] = {"gemm_nn_splitk", "gemm_nt_splitk", "gemm_tn_splitk"};
     const int l = p.layout == LAYOUT_NN ? 0 : p.layout == LAYOUT_NT ? 1 : p.layout == LAYOUT_TN ? 2 : -1;
     if (l < 0) return "gemm_?";
+    if (p.seg > 0) {
+        const TileCfg c = pick_tile(p);
+        return c == T_128 ? "gemm_nt_seg128" : c == T_64x128 ? "gemm_nt_seg64x128" : "gemm_nt_seg64";
+    }
     return p.splits > 1 ? split[l] : names[l][pick_tile(p)];
 }
 
@@ -1071,10 +1116,29 @@ bool nn_large_tiles(int64_t M, int64_t N) {
     return cost(256, 1.0) <= 1.05 * cost(160, 0.8);
 }
 
-int nt_split_limit(int64_t M, int64_t N, int64_t K) { return split_limit(M, N, K); }
-
 int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit) {
     return pick_splits(M, N, K, ksplit);
+}
+
+// A split product keeps its plan's sums either as slabs or in the tile (SEG),
+// whichever the model has faster.  Slabs up to 16 MB are read back from the
+// caches (10 TB/s); larger ones cost their reads and the sum's write at 3.3
+// TB/s.  With two lanes the chunks of a product in the tile run side by side,
+// as one product of twice the rows; slabs are shared, so their chunks cannot.
+// One stream takes the tile only when it gains 10%.  (2048 x 8192 -> 1024 in
+// four splits: h = 4096 row backward 1520 us with slabs, 1536 in the tile;
+// 512 x 6144 -> 9216 in two, 512 x 12288 -> 6144 in three: h = 12288 forward
+// 1367 us with slabs on one stream, 1196 in the tile on two.)
+bool nt_plan_in_tile(int64_t M, int64_t N, int64_t K, bool lanes) {
+    int64_t ks = 0;
+    const int S = pick_splits(M, N, K, &ks);
+    if (S <= 1) return false;
+    const double el = (double)M * (double)N;
+    double slabs = 0.0, tile = 0.0;
+    pick_tile(LAYOUT_NT, M, N, ks, S, false, &slabs);
+    slabs += 4.0 * S * el <= 16e6 ? 4.0 * S * el / 1e7 : 4.0 * (S + 1) * el / 3.3e6;
+    pick_seg_tile(lanes ? 2 * M : M, N, K, &tile);
+    return lanes ? 0.5 * tile < slabs : tile < 0.9 * slabs;
 }
 
 hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
@@ -1086,6 +1150,8 @@ hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
     const bool b16 = p.out_bf16;
     if (p.nparts > kMaxFusedParts || (p.nparts > 1 && (p.splits > 1 || p.own < 0 ||
                                                        p.own >= p.nparts || p.ldp % 4)))
+        return hipErrorInvalidValue;
+    if (p.seg > 0 && (p.layout != LAYOUT_NT || p.splits > 1 || p.epi != EPI_NONE || p.seg % 64))
         return hipErrorInvalidValue;
     if (p.splits > 1) {
         // split-K: plain fp32 outputs, whole K steps per split, every split
@@ -1113,6 +1179,7 @@ hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
             return hipErrorInvalidValue;
         }
     case LAYOUT_NT:   // dY W^T with B = W (contiguous along the contraction)
+        if (p.seg > 0) return b16 ? launch_seg<true>(p, s) : launch_seg<false>(p, s);
         if (p.epi == EPI_NONE)
             return b16 ? launch_tiles<true, true, EPI_NONE, true>(p, s)
                        : launch_tiles<true, true, EPI_NONE, false>(p, s);

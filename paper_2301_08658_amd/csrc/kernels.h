@@ -32,6 +32,9 @@ struct GemmProblem {
     // ksplit a multiple of 64, every split non-empty
     int splits = 1;
     int64_t ksplit = 0, c_split = 0;
+    // NT, EPI_NONE, no split: > 0 sums segments of seg k (a multiple of 64)
+    // one after the other in the tile, the bits of that split's slab sum
+    int64_t seg = 0;
     // fused peer sum (NN, no split): when nparts > 1 the epilogue forms
     // sum_{j < nparts} P_j in group order before bias / GeLU, with P_own the
     // tile's own accumulators and the others read from peers[j] (fp32, ld ldp)
@@ -49,13 +52,14 @@ const char* gemm_kernel_name(const GemmProblem& p);
 
 // Split-K plan for an NT product [M, N] over K written to fp32: returns the
 // split count S (1: no split) and the k per split (a multiple of 64; the
-// last split may be shorter).  The plan depends on M, N and K only and never
-// exceeds nt_split_limit, by which the slabs are sized; S * (256-row tiles) *
-// (160-column tiles) is at most kMaxSplitTiles there.
+// last split may be shorter).  The plan depends on M, N and K only; S *
+// (256-row tiles) * (160-column tiles) never exceeds kMaxSplitTiles.
 constexpr int kMaxSplits = 16;
 constexpr int64_t kMaxSplitTiles = 512;
-int nt_split_limit(int64_t M, int64_t N, int64_t K);
 int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit);
+// True when a product with a split plan forms its sums in one launch (seg)
+// rather than in slabs; lanes: its chunks may run on two streams then.
+bool nt_plan_in_tile(int64_t M, int64_t N, int64_t K, bool lanes);
 // Modelled time (us) of an unsplit product on the tiles it would take.
 double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K);
 // Modelled time (us) that an unsplit product loses by reading B along its rows

@@ -116,3 +116,61 @@ def test_split_repeated_calls_identical():
         assert torch.equal(a[key], b[key]), key
     for key in ("dh_pre", "dx_qkv", "dx_fc1", "d_attn"):
         assert torch.equal(ba[key], bb[key]), key
+
+
+def split_plan(M, N, K):
+    """(S, k per split) of a chunk product: the least of (rounds of 256 tiles
+    of 256 x 160) x (k per split) x (flops per k) + 8 bytes of slab traffic per
+    split and element, taken when it gains 15%."""
+    tiles, per_k = -(-M // 256) * -(-N // 160), 2 * 256 * 160
+    plain = -(-tiles // 256) * K * per_k
+    best = (plain, 1, K)
+    for s in range(2, 17):
+        ks = -(-(-(-K // s)) // 64) * 64
+        if ks >= 256 and -(-K // ks) == s and tiles * s <= 512:
+            best = min(best, (-(-tiles * s // 256) * ks * per_k + 8 * s * M * N, s, ks),
+                       key=lambda c: c[0])
+    return (1, K) if best[0] > 0.85 * plain else best[1:]
+
+
+# (mesh, tokens, h, chunks, same stream, partials, names of split products):
+# slabs and every tile that sums the segments itself, on one and two lanes
+ORDER_CASES = [
+    ((2, 2), 512, 4096, 1, True, torch.float32, ("seg128", "seg64")),
+    ((2, 2), 1024, 4096, 2, False, torch.bfloat16, ("seg128",)),
+    ((2, 2), 1024, 2000, 2, False, torch.float32, ("seg64x128", "splitk")),
+    ((2, 2), 1000, 2000, 1, True, torch.float32, ("seg64",)),
+    ((4, 2), 1600, 2048, 2, False, torch.bfloat16, ("seg64x128",)),
+    ((2, 2), 200, 2000, 1, True, torch.bfloat16, ("splitk",)),
+]
+
+
+@pytest.mark.parametrize("mesh,T,h,chunks,same,pdt,kinds", ORDER_CASES)
+def test_own_partials_are_the_plans_splits_summed_in_order(mesh, T, h, chunks, same, pdt, kinds):
+    """An own partial has the bits of the plan's splits, each a product over
+    its k range, added in split order in fp32, whether they went through slabs
+    or were added in the tile, and on whichever tile and stream."""
+    print(f"split order {mesh} T={T} h={h} chunks={chunks}", flush=True)
+    inp = make_block_inputs("col", mesh, (1, 0), T, h, 0.02, seed=46, on_device=True,
+                            partial_dtype=pdt)
+    out = {}
+    names = _profiled_names(lambda: out.update(run_block_fwd(
+        inp, chunks, same_stream=same, workspace=True)))
+    for kind in kinds:
+        assert any(n.startswith(f"gemm_nt_{kind}_") for n in names), (kind, names)
+    one, some = atp.mesh(1, 1), False
+    for i, g in enumerate(inp["G"][:3]):
+        if g.red_size == 1:
+            continue
+        S, ks = split_plan(T // chunks, g.n_loc, g.k_loc)
+        some |= S > 1
+        xin, want = (inp["a"] if i == 1 else inp["x"]), None
+        for k0 in range(0, g.k_loc, ks):
+            k1 = min(k0 + ks, g.k_loc)
+            y = torch.empty((T, g.n_loc), device=xin.device)
+            atp.atp_shard_linear_fwd(one, 0, T, k1 - k0, g.n_loc, 1, xin[:, k0:k1].contiguous(),
+                                     inp["wkn"][i][k0:k1], None, atp.ATP_EPI_NONE, y)
+            want = y if want is None else want + y
+        torch.cuda.synchronize()
+        assert torch.equal(out["own"][i], want.to(pdt)), LIN[i]
+    assert some
