@@ -417,14 +417,17 @@ bool fwd_may_copy_w(const BlockPlan& P, int L, int64_t tokens) {
 // stored [k][n] as they are on the workspace path: there is no place for a
 // copy, or its products are not split over k and would not gain from W^T what
 // copying it costs (4 us and its bytes read and written at 3.5 TB/s).  Split
-// products run from W^T.
-bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks) {
+// products run from W^T, and so do all in a captured call that do not fill 256 x
+// 256 tiles: the launches of the direct path are not captured (see
+// refuse_capture_of_direct_path).
+bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks, bool capturing) {
     if (!fwd_may_copy_w(P, L, tokens)) return true;
     const atp_shard& g = P.g[L];
     const bool one = g.red_size <= 1;
     const int64_t m = one ? tokens : tokens / chunks;
     int64_t ks = 0;
     if (!one && atp::nt_split_plan(m, g.n_loc, g.k_loc, &ks) > 1) return false;
+    if (capturing) return atp::nn_large_tiles(m, g.n_loc);
     const double copy = 4.0 + 4.0 * (double)g.k_loc * (double)g.n_loc / 3.5e6;
     return (one ? 1 : chunks) * atp::nn_extra_us(m, g.n_loc, g.k_loc) < copy;
 }
@@ -564,6 +567,7 @@ const char* const kLinearName[4] = {"qkv", "out", "fc1", "fc2"};
 constexpr double kInlineBytes = 8e6;   // one chunk's reduction, read and written
 struct Streams {
     hipStream_t cs, ms;
+    bool capturing = false;    // cs is under graph capture
     bool may_inline = false;   // two streams and no capture
     bool ms_used = false, cs_joined = false;
     hipEvent_t* ev = nullptr;  // three events: ms before the call, after it, cs after it
@@ -571,10 +575,10 @@ struct Streams {
 
     atp_status begin(hipEvent_t* events) {
         ev = events;
-        if (ms == cs) return ATP_OK;
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         HIP_CHECK(hipStreamIsCapturing(cs, &cap), "hipStreamIsCapturing");
-        may_inline = cap == hipStreamCaptureStatusNone;
+        capturing = cap != hipStreamCaptureStatusNone;
+        may_inline = ms != cs && !capturing;
         return ATP_OK;
     }
     // Queued first when some reduction will run on ms: ms waits for what cs
@@ -1204,7 +1208,9 @@ atp_status weight_grads_ws(const atp_shard& g, bool kn, const void* X, int64_t l
 // copy 3.5 us and its bytes at 4.8 TB/s (8192 x 6144 41 us), the column sum 4 us
 // and dY at 5 TB/s (h = 4096 layer backward 1577 -> 1561 us, attention block
 // forward and backward 993 -> 978).  The wide layer's dW (256 x 256 tiles, 16%
-// slower TN) run from copies.  Both give the same bits.
+// slower TN) run from copies.  Both give the same bits.  A captured call always
+// takes the copies: the launches of the direct path are not captured (see
+// refuse_capture_of_direct_path).
 bool dw_direct(const atp_shard& g, bool kn, int64_t T, bool copy_x, bool db) {
     const int64_t M = kn ? g.k_loc : g.n_loc, N = kn ? g.n_loc : g.k_loc;
     auto copy = [&](int64_t cols) { return 3.5 + 4.0 * (double)T * (double)cols / 4.8e6; };
@@ -1344,7 +1350,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
             for (int L = 0; L < 4; ++L)
                 if (fwd_may_copy_w(P, L, tokens)) {
                     uint16_t* t = c.take((size_t)P.g[L].n_loc * ws_pitch(P.g[L].k_loc) * 2);
-                    if (!fwd_reads_w(P, L, tokens, chunks)) wt[L] = t;
+                    if (!fwd_reads_w(P, L, tokens, chunks, S.capturing)) wt[L] = t;
                 }
         slab = reinterpret_cast<float*>(c.take(slab_bytes(P, tokens, false)));
     }
@@ -1641,7 +1647,8 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         const atp_shard& g = P.g[L];
         if (L == 2) ATP_CHECK(wait_dpre(chunks - 1));
         const int xi = xsrc[L];
-        if (!ws || dw_direct(g, kn, tokens, !xt_done[xi], io->db[L] != nullptr))
+        if (!ws || (!S.capturing &&
+                    dw_direct(g, kn, tokens, !xt_done[xi], io->db[L] != nullptr)))
             return weight_grads(g, kn, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L], w->ldw[L],
                                 io->db[L], tokens, S.cs);
         // X^T once per source (x serves QKV and fc1), dY^T, then the NT
@@ -1718,6 +1725,14 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     // only that path may run under graph capture.
     const bool ws = workspace && ws_bytes >= ws_fwd_bytes(P, T, w->layout, 2);
     if (!ws) ATP_CHECK(refuse_capture_of_direct_path(compute_stream));
+    Streams S(compute_stream, comm_stream);
+    hipEvent_t* ev = nullptr;
+    // [0..2] the streams'  [3] QKV reduced  [4] out-proj done, then the chunk
+    // events of QKV and of out-proj
+    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
+    ATP_CHECK(S.begin(ev));
+    hipEvent_t qkv_done = ev[3], o_done = ev[4];
+
     uint16_t* wt[2] = {nullptr, nullptr};
     float* slab = nullptr;
     if (ws) {
@@ -1726,18 +1741,10 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
             for (int L = 0; L < 2; ++L)
                 if (fwd_may_copy_w(P, L, T)) {
                     uint16_t* t = c.take((size_t)P.g[L].n_loc * ws_pitch(P.g[L].k_loc) * 2);
-                    if (!fwd_reads_w(P, L, T, chunks)) wt[L] = t;
+                    if (!fwd_reads_w(P, L, T, chunks, S.capturing)) wt[L] = t;
                 }
         slab = reinterpret_cast<float*>(c.take(slab_bytes(P, T, false, 2)));
     }
-
-    Streams S(compute_stream, comm_stream);
-    hipEvent_t* ev = nullptr;
-    // [0..2] the streams'  [3] QKV reduced  [4] out-proj done, then the chunk
-    // events of QKV and of out-proj
-    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
-    ATP_CHECK(S.begin(ev));
-    hipEvent_t qkv_done = ev[3], o_done = ev[4];
     auto make = [&](int L) {
         return [&, L](const void* A, void* C, int64_t ldc, bool b16, int epi, int64_t M) {
             const int64_t lda = L == 0 ? io->ldx : io->ld_attn;
@@ -1853,15 +1860,15 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
         dyt_o = c.take(go.n_loc * t2);
         colpart = reinterpret_cast<float*>(c.take(colpart_bytes(P, T)));
     }
+    Streams S(compute_stream, comm_stream);
     auto dweights = [&](const atp_shard& g, int L, const void* X, int64_t ldx, const void* dY,
                         int64_t lddy, uint16_t* xt, uint16_t* dyt, hipStream_t s) {
-        if (ws && !dw_direct(g, kn, T, true, io->db[L] != nullptr))
+        if (ws && (S.capturing || !dw_direct(g, kn, T, true, io->db[L] != nullptr)))
             return weight_grads_ws(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T,
                                    xt, dyt, colpart, s);
         return weight_grads(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T, s);
     };
 
-    Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
     // [0..2] the streams'  [3] d_attn reduced  [4] QKV dX done, then the chunk
     // events of out-proj's dX and of QKV's dX

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def _block_call(inp, chunks, workspace):
+def _block_call(inp, chunks, workspace, ws=None):
     """Preallocated outputs and a function that runs fwd then bwd (the
     backward consumes the forward's H and pre-activation) on the current
     stream, with side streams made once."""
@@ -36,7 +36,7 @@ def _block_call(inp, chunks, workspace):
                dx_qkv=bf(T, G[0].k_loc), dx_fc1=bf(T, G[2].k_loc), d_attn=bf(T, G[1].k_loc))
     out.update({f"dw{i}": torch.empty((g.k_loc, g.n_loc), device=DEV) for i, g in enumerate(G)})
     out.update({f"db{i}": torch.empty((g.n_loc,), device=DEV) for i, g in enumerate(G)})
-    ws = block_workspace(inp) if workspace else None
+    ws = block_workspace(inp) if workspace and ws is None else ws
     ms = torch.cuda.Stream()
 
     def call():
@@ -147,7 +147,7 @@ def test_capture_refused_on_direct_path(case):
     assert torch.all(marker == 1.0)
 
 
-def _attention_block_call(case, seed, workspace):
+def _attention_block_call(case, seed, workspace, keep=None):
     """Seeded inputs of one device's attention block (other members' data
     in place), preallocated outputs, and a function running its forward
     then backward on the current stream."""
@@ -187,6 +187,8 @@ def _attention_block_call(case, seed, workspace):
     if workspace:
         ws = torch.empty(atp.atp_block_workspace_bytes(m, bm, T, h, chunks), dtype=torch.uint8,
                          device=DEV)
+    if keep is not None:
+        keep.update(x=x, ws=ws)
     ms = torch.cuda.Stream()
 
     def call():
@@ -236,6 +238,81 @@ def test_attention_block_graph_replay_equals_eager(case):
             view = torch.int16 if v.element_size() == 2 else torch.int32
             assert torch.equal(v.view(view), ref[k].view(view)), f"replay {rep}: {k}"
     del other_out
+
+
+def _starts_with_transpose(ws, x):
+    """Whether the backward's first workspace piece holds X^T (rows of
+    tokens + 64 values)."""
+    T, k = x.shape
+    piece = ws.view(torch.bfloat16)[:k * (T + 64)].view(k, T + 64)[:, :T]
+    return torch.equal(piece, x.t())
+
+
+@pytest.mark.parametrize("attention", [False, True], ids=["block", "attention_block"])
+def test_captured_weight_gradients_run_from_copies(attention):
+    """A captured backward forms dW from the workspace's transposed copies,
+    also at sizes where an eager call reads X and dY as given."""
+    print(f"captured dW attention={attention}", flush=True)
+    if attention:
+        keep = {}
+        _, call = _attention_block_call(ATTN_CASES[0], 38, True, keep)
+        ws, x = keep["ws"], keep["x"]
+    else:
+        inp = make_block_inputs("col", (2, 4), (1, 2), 512, 1024, 0.02, seed=39, bwd=True)
+        ws, x = block_workspace(inp), inp["x"]
+        _, call = _block_call(inp, 4, True, ws)
+    ws.zero_()
+    call()
+    torch.cuda.synchronize()
+    assert not _starts_with_transpose(ws, x), "the eager call took the copies: choose another size"
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(2):
+        ws.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert _starts_with_transpose(ws, x)
+
+
+def test_captured_forward_runs_from_weight_copies():
+    """A captured forward whose products do not fill 256 x 256 tiles runs them
+    from W^T in the workspace, also where an eager call reads W as given."""
+    print("captured forward", flush=True)
+    inp = make_block_inputs("col", (2, 2), (1, 0), 1024, 512, 0.02, seed=40, bwd=True)
+    G, ws = inp["G"], block_workspace(inp)
+    m, mode = inp["m"], block_mode_code("col")
+    bf = lambda c: torch.empty((1024, c), dtype=torch.bfloat16, device=DEV)  # noqa: E731
+    tabs = [group_table(torch.empty((1024, g.n_loc), device=DEV), inp["peers"][i], g.red_index)
+            for i, g in enumerate(G)]
+    qkv, o, hh, pre, z = (bf(G[i].n_loc) for i in (0, 1, 2, 2, 3))
+    ms = torch.cuda.Stream()
+
+    def call():
+        atp.atp_block_fwd(m, mode, 1024, 512, 1, inp["w"], inp["b"], inp["x"], inp["a"], tabs, qkv,
+                          o, hh, pre, z, workspace=ws,
+                          compute_stream=torch.cuda.current_stream(), comm_stream=ms)
+
+    def w_copied():   # the first piece is QKV's W^T (rows of k_loc + 64 values)
+        k, n = G[0].k_loc, G[0].n_loc
+        piece = ws.view(torch.bfloat16)[:n * (k + 64)].view(n, k + 64)[:, :k]
+        return torch.equal(piece, inp["wkn"][0].t())
+
+    ws.zero_()
+    call()
+    torch.cuda.synchronize()
+    assert not w_copied(), "the eager call copied W: choose another size"
+    ref = [t.clone() for t in (qkv, o, hh, pre, z)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        call()
+    for _ in range(2):
+        ws.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert w_copied()
+        for t, r in zip((qkv, o, hh, pre, z), ref):
+            assert torch.equal(t, r)
 
 
 def test_attention_block_capture_refused_without_workspace():
