@@ -369,7 +369,8 @@ atp_status atp_transpose_bf16(int64_t rows, int64_t cols, const void* src, int64
  * ordered after all of it; the workspace may be reused once compute_stream
  * reaches that point.  A call that would take the direct path refuses a
  * compute_stream under HIP graph capture (UNSUPPORTED) before enqueueing
- * anything.  Concurrent calls from different host threads are safe (each
+ * anything, and every block call refuses a comm_stream under capture whose
+ * compute_stream is not.  Concurrent calls from different host threads are safe (each
  * thread keeps its own synchronisation events). */
 atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t tokens, int64_t h,
                          int32_t chunks, const atp_block_weights* w,

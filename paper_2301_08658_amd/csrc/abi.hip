@@ -578,6 +578,14 @@ struct Streams {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         HIP_CHECK(hipStreamIsCapturing(cs, &cap), "hipStreamIsCapturing");
         capturing = cap != hipStreamCaptureStatusNone;
+        if (ms != cs && !capturing) {
+            // cs would join a capture of ms at its first wait for it, halfway
+            // through the call
+            HIP_CHECK(hipStreamIsCapturing(ms, &cap), "hipStreamIsCapturing");
+            if (cap != hipStreamCaptureStatusNone)
+                return set_error(ATP_ERR_UNSUPPORTED,
+                                 "comm_stream is under graph capture, compute_stream is not");
+        }
         may_inline = ms != cs && !capturing;
         return ATP_OK;
     }

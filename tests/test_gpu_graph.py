@@ -350,3 +350,39 @@ def test_attention_block_capture_refused_without_workspace():
     g.replay()
     torch.cuda.synchronize()
     assert torch.all(marker == 1.0)
+
+
+@pytest.mark.parametrize("mesh,coord", [((2, 2), (1, 0)), ((1, 1), (0, 0))],
+                         ids=["inlined", "no_reduction"])
+def test_capture_of_the_comm_stream_alone_refused(mesh, coord):
+    """A call whose comm stream is being captured and whose compute stream is
+    not is refused before it enqueues anything: joining that capture halfway
+    would leave part of the call's work in the graph.  The capture (one fill
+    kernel) ends normally, and nothing was written."""
+    print(f"comm stream capture {mesh}", flush=True)
+    T, h = 256, 512
+    inp = make_block_inputs("col", mesh, coord, T, h, 0.02, seed=41, bwd=True)
+    G, m, mode = inp["G"], inp["m"], block_mode_code("col")
+    nan = lambda c, dt=torch.bfloat16: torch.full((T, c), float("nan"), dtype=dt,  # noqa: E731
+                                                  device=DEV)
+    tabs = [group_table(nan(g.n_loc, torch.float32), inp["peers"][i], g.red_index)
+            if g.red_size > 1 else None for i, g in enumerate(G)]
+    out = [nan(G[i].n_loc) for i in (0, 1, 2, 2, 3)]
+    marker = torch.zeros(64, device=DEV)
+    cs, comm = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g, err = torch.cuda.CUDAGraph(), None
+    with torch.cuda.graph(g, stream=comm):
+        marker.fill_(1.0)
+        try:
+            atp.atp_block_fwd(m, mode, T, h, 2, inp["w"], inp["b"], inp["x"], inp["a"], tabs, *out,
+                              compute_stream=cs, comm_stream=comm)
+        except atp.AtpError as e:
+            err = e
+    torch.cuda.synchronize()
+    assert err is not None and err.status == atp.ATP_ERR_UNSUPPORTED, err
+    assert "comm_stream" in str(err)
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.all(marker == 1.0)
+    assert all(torch.isnan(t).all() for t in out)
