@@ -366,8 +366,9 @@ atp_status atp_transpose_bf16(int64_t rows, int64_t cols, const void* src, int64
  * are the same for every chunk count that gives each chunk product the same
  * split plan (without a workspace: every chunk count).  compute_stream's
  * earlier work happens before the block's, and on return compute_stream is
- * ordered after all of it; the workspace may be reused once compute_stream
- * reaches that point.  A call that would take the direct path refuses a
+ * ordered after all of it and after comm_stream's earlier work; the workspace
+ * may be reused once compute_stream reaches that point.  comm_stream is
+ * ordered after compute_stream's earlier work, with or without reductions.  A call that would take the direct path refuses a
  * compute_stream under HIP graph capture (UNSUPPORTED) before enqueueing
  * anything, and every block call refuses a comm_stream under capture whose
  * compute_stream is not.  Concurrent calls from different host threads are safe (each

@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <initializer_list>
 #include <map>
 #include <mutex>
 #include <string>
@@ -563,13 +564,13 @@ const char* const kLinearName[4] = {"qkv", "out", "fc1", "fc2"};
 // whose chunk reductions move 28-38 MB, took 1414 us instead of 1210).
 // They still come after everything queued on ms before the call, and ms after
 // the call is ordered after them.  Under graph capture every reduction runs
-// on ms (ms joins the capture when it first waits for a product).
+// on ms.
 constexpr double kInlineBytes = 8e6;   // one chunk's reduction, read and written
 struct Streams {
     hipStream_t cs, ms;
     bool capturing = false;    // cs is under graph capture
     bool may_inline = false;   // two streams and no capture
-    bool ms_used = false, cs_joined = false;
+    bool opened = false, cs_joined = false;
     hipEvent_t* ev = nullptr;  // three events: ms before the call, after it, cs after it
     Streams(void* c, void* m) : cs(static_cast<hipStream_t>(c)), ms(static_cast<hipStream_t>(m)) {}
 
@@ -589,12 +590,14 @@ struct Streams {
         may_inline = ms != cs && !capturing;
         return ATP_OK;
     }
-    // Queued first when some reduction will run on ms: ms waits for what cs
-    // held before the call.  (Its first product's event would order it as
+    // Queued first unless all reductions run on cs: ms waits for what cs
+    // held before the call (also in a call without reductions, and under
+    // capture, where ms joins it so).  (A product's event would order it as
     // well; this early packet has ms's queue awake by then: 945 against 934 us
     // for a 922 us forward and backward.)
-    atp_status open(hipEvent_t start) const {
-        if (ms == cs) return ATP_OK;
+    atp_status open(hipEvent_t start) {
+        if (ms == cs || opened) return ATP_OK;
+        opened = true;
         HIP_CHECK(hipEventRecord(start, cs), "hipEventRecord");
         HIP_CHECK(hipStreamWaitEvent(ms, start, 0), "hipStreamWaitEvent");
         return ATP_OK;
@@ -603,6 +606,16 @@ struct Streams {
     bool inlined(int64_t rows, int64_t cols, int parts, bool b16) const {
         return may_inline &&
                (double)rows * (double)cols * (parts * (b16 ? 2.0 : 4.0) + 2.0) <= kInlineBytes;
+    }
+    // whether there are reductions and all of them run on cs
+    static bool all_inlined(const bool* inl, std::initializer_list<int32_t> groups) {
+        bool any = false;
+        for (int32_t g : groups) {
+            if (g > 1 && !*inl) return false;
+            any |= g > 1;
+            ++inl;
+        }
+        return any;
     }
     // The stream of a reduction whose product was just queued on st (cs, when
     // the reduction is inlined): ordered after it; `done` marks the product.
@@ -619,14 +632,13 @@ struct Streams {
         }
         HIP_CHECK(hipEventRecord(done, st), "hipEventRecord");
         HIP_CHECK(hipStreamWaitEvent(ms, done, 0), "hipStreamWaitEvent");
-        ms_used = true;
         *rs = ms;
         return ATP_OK;
     }
-    // cs is ordered after all of the block's work on ms, and ms after the
-    // reductions on cs
+    // cs is ordered after all of the block's (and earlier) work on ms, and ms
+    // after the reductions on cs
     atp_status end() const {
-        if (ms_used) {
+        if (opened) {
             HIP_CHECK(hipEventRecord(ev[1], ms), "hipEventRecord");
             HIP_CHECK(hipStreamWaitEvent(cs, ev[1], 0), "hipStreamWaitEvent");
         }
@@ -1168,7 +1180,6 @@ atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* 
     }
     const int64_t mc = T / chunks;
     const bool inl = S.inlined(mc, ncols, red_size, pb16);
-    if (!inl && !S.ms_used) ATP_CHECK(S.open(*done));   // (*done is recorded again below)
     void* own = parts[red_index];
     for (int32_t c = 0; c < chunks; ++c) {
         const int64_t r0 = (int64_t)c * mc;
@@ -1396,11 +1407,8 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     bool inl[4];
     for (int L = 0; L < 4; ++L)
         inl[L] = S.inlined(mc, P.g[L].n_loc, P.g[L].red_size, pb16);
-    for (int L = 0; L < 4; ++L)
-        if (P.g[L].red_size > 1 && !inl[L]) {
-            ATP_CHECK(S.open(ev[5]));
-            break;
-        }
+    if (!S.all_inlined(inl, {P.g[0].red_size, P.g[1].red_size, P.g[2].red_size, P.g[3].red_size}))
+        ATP_CHECK(S.open(ev[5]));
     // fc1's H is reduced on ms
     const bool fc1_reduced = P.g[2].red_size > 1 && S.ms != S.cs && !inl[2];
 
@@ -1575,11 +1583,8 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     bool inl[4];
     for (int L = 0; L < 4; ++L)
         inl[L] = S.inlined(mc, P.g[L].k_loc, P.g[L].bwd_size, pb16);
-    for (int L = 0; L < 4; ++L)
-        if (P.g[L].bwd_size > 1 && !inl[L]) {
-            ATP_CHECK(S.open(ev[3]));
-            break;
-        }
+    if (!S.all_inlined(inl, {P.g[0].bwd_size, P.g[1].bwd_size, P.g[2].bwd_size, P.g[3].bwd_size}))
+        ATP_CHECK(S.open(ev[3]));
     // fc2's dX is reduced on ms
     const bool fc2_reduced = P.g[3].bwd_size > 1 && S.ms != S.cs && !inl[3];
 
@@ -1735,11 +1740,14 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     if (!ws) ATP_CHECK(refuse_capture_of_direct_path(compute_stream));
     Streams S(compute_stream, comm_stream);
     hipEvent_t* ev = nullptr;
-    // [0..2] the streams'  [3] QKV reduced  [4] out-proj done, then the chunk
-    // events of QKV and of out-proj
-    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
+    // [0..2] the streams'  [3] QKV reduced  [4] out-proj done  [5] start, then
+    // the chunk events of QKV and of out-proj
+    ATP_CHECK(sync_events(6 + 2 * (size_t)chunks, &ev));
     ATP_CHECK(S.begin(ev));
     hipEvent_t qkv_done = ev[3], o_done = ev[4];
+    const bool inl[2] = {S.inlined(T / chunks, gq.n_loc, gq.red_size, pb16),
+                         S.inlined(T / chunks, go.n_loc, go.red_size, pb16)};
+    if (!S.all_inlined(inl, {gq.red_size, go.red_size})) ATP_CHECK(S.open(ev[5]));
 
     uint16_t* wt[2] = {nullptr, nullptr};
     float* slab = nullptr;
@@ -1772,7 +1780,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     ATP_CHECK(need_wt(0));
     ATP_CHECK(chained_linear(S, gq.red_size, gq.red_index, io->qkv_partials, io->ldp_qkv, pb16,
                              io->x_loc, io->ldx, gq.n_loc, atp::EPI_BIAS, w->b[0], nullptr,
-                             io->qkv, io->ld_qkv, T, chunks, ev + 5, &qkv_done, make(0), slab));
+                             io->qkv, io->ld_qkv, T, chunks, ev + 6, &qkv_done, make(0), slab));
     // a causal sequence spans chunks: the core waits for the whole QKV block
     if (qkv_done) HIP_CHECK(hipStreamWaitEvent(S.cs, qkv_done, 0), "hipStreamWaitEvent");
     if (T > 0) {
@@ -1796,7 +1804,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     ATP_CHECK(need_wt(1));
     ATP_CHECK(chained_linear(S, go.red_size, go.red_index, io->o_partials, io->ldp_o, pb16,
                              io->attn, io->ld_attn, go.n_loc, atp::EPI_BIAS, w->b[1], nullptr,
-                             io->o, io->ld_o, T, chunks, ev + 5 + chunks, &o_done, make(1), slab));
+                             io->o, io->ld_o, T, chunks, ev + 6 + chunks, &o_done, make(1), slab));
     return S.end();
 }
 
@@ -1878,11 +1886,14 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     };
 
     hipEvent_t* ev = nullptr;
-    // [0..2] the streams'  [3] d_attn reduced  [4] QKV dX done, then the chunk
-    // events of out-proj's dX and of QKV's dX
-    ATP_CHECK(sync_events(5 + 2 * (size_t)chunks, &ev));
+    // [0..2] the streams'  [3] d_attn reduced  [4] QKV dX done  [5] start, then
+    // the chunk events of out-proj's dX and of QKV's dX
+    ATP_CHECK(sync_events(6 + 2 * (size_t)chunks, &ev));
     ATP_CHECK(S.begin(ev));
     hipEvent_t da_done = ev[3], dx_done = ev[4];
+    const bool inl[2] = {S.inlined(T / chunks, gq.k_loc, gq.bwd_size, pb16),
+                         S.inlined(T / chunks, go.k_loc, go.bwd_size, pb16)};
+    if (!S.all_inlined(inl, {gq.bwd_size, go.bwd_size})) ATP_CHECK(S.open(ev[5]));
     auto make = [&](int L, const void* dY, int64_t lddy) {
         return [&, L, lddy](const void* A, void* C, int64_t ldc, bool b16, int epi, int64_t M) {
             return dyw_problem(P.g[L], kn, w->w[L], w->ldw[L], A, lddy, C, ldc, b16, epi, M);
@@ -1892,7 +1903,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     // on cs while those reductions drain
     ATP_CHECK(chained_linear(S, go.bwd_size, go.bwd_index, io->d_attn_partials, io->ldp_da, pb16,
                              io->d_o, io->ld_do, go.k_loc, atp::EPI_NONE, nullptr, nullptr,
-                             io->d_attn, io->ld_d_attn, T, chunks, ev + 5, &da_done,
+                             io->d_attn, io->ld_d_attn, T, chunks, ev + 6, &da_done,
                              make(1, io->d_o, io->ld_do)));
     ATP_CHECK(dweights(go, 1, io->attn, io->ld_attn, io->d_o, io->ld_do, xt_a, dyt_o, S.cs));
     // the core's backward reads the device's columns of the whole d_attn
@@ -1923,7 +1934,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     // QKV: dX chunks from the gathered d_qkv (reduced on ms into dx), dW, db
     ATP_CHECK(chained_linear(S, gq.bwd_size, gq.bwd_index, io->dx_partials, io->ldp_dx, pb16,
                              io->d_qkv, io->ld_dqkv, gq.k_loc, atp::EPI_NONE, nullptr, nullptr,
-                             io->dx, io->ld_dx, T, chunks, ev + 5 + chunks, &dx_done,
+                             io->dx, io->ld_dx, T, chunks, ev + 6 + chunks, &dx_done,
                              make(0, io->d_qkv, io->ld_dqkv)));
     ATP_CHECK(dweights(gq, 0, io->x_loc, io->ldx, io->d_qkv, io->ld_dqkv, xt_x, dyt_q, S.cs));
     return S.end();

@@ -437,3 +437,34 @@ def test_reductions_keep_their_place_on_the_comm_stream(T, h, chunks):
         torch.cuda.synchronize()
         for k in keys:
             assert torch.equal(_bits(seen[k]), _bits(want[k])), (T, k)
+
+
+@pytest.mark.parametrize("bwd", [False, True], ids=["fwd", "bwd"])
+@pytest.mark.parametrize("mesh", [(1, 1), (2, 2)], ids=["no_reduction", "inlined"])
+def test_call_orders_both_streams(mesh, bwd):
+    """A call orders comm_stream after compute_stream's earlier work and
+    compute_stream after comm_stream's, also when it has no reduction."""
+    print(f"stream order {mesh} bwd={bwd}", flush=True)
+    inp = make_block_inputs("col", mesh, (0, 0), 128, 512, 0.02, seed=72, on_device=True, bwd=True)
+    big = torch.empty(64 << 20, device=DEV)
+    flags, seen = torch.zeros(2, device=DEV), torch.zeros(2, device=DEV)
+    comm = torch.cuda.Stream()
+    run = run_block_bwd if bwd else run_block_fwd
+    run(inp, 1, comm=comm)                         # the library is warm
+    torch.cuda.synchronize()
+
+    def late(i):
+        for _ in range(20):
+            big.fill_(1.0)                         # about a millisecond
+        flags[i:i + 1].fill_(1.0)
+    with torch.cuda.stream(comm):
+        late(0)
+    run(inp, 1, comm=comm)
+    seen[0:1].copy_(flags[0:1])
+    torch.cuda.synchronize()
+    late(1)
+    run(inp, 1, comm=comm)
+    with torch.cuda.stream(comm):
+        seen[1:2].copy_(flags[1:2])
+    torch.cuda.synchronize()
+    assert seen.tolist() == [1.0, 1.0]
