@@ -9,6 +9,8 @@ identified).  The library refuses a capturing stream whenever a call would
 take the direct path (no workspace, one smaller than the pass needs, or a
 backward with tokens % 8 != 0), before it enqueues anything, and the direct
 cases here stay skipped."""
+import gc
+
 import pytest
 import torch
 
@@ -17,6 +19,18 @@ from helpers import block_mode_code, block_workspace, group_table, make_block_in
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+
+
+@pytest.fixture(autouse=True)
+def _no_collection_during_a_capture():
+    """An earlier test's graph can be left in a reference cycle (a caught
+    error's traceback holds the test's frame).  Collected while another
+    capture is under way, its destructor makes calls that a capture does not
+    allow, and the process aborts: collect before each test, not within."""
+    gc.collect()
+    gc.disable()
+    yield
+    gc.enable()
 
 
 def _block_call(inp, chunks, workspace, ws=None):
