@@ -338,7 +338,8 @@ atp_status atp_transpose_bf16(int64_t rows, int64_t cols, const void* src, int64
  * chunk's reduction runs on comm_stream as soon as that chunk's partial is
  * written (one that moves at most 8 MB is too short to hide anything and runs
  * on compute_stream, except under graph capture: still after comm_stream's
- * earlier work, and comm_stream is ordered after it when the call returns);
+ * earlier work, behind the products that need no result of it, and
+ * comm_stream is ordered after it when the call returns);
  * fc2's chunk c waits for fc1's reduced chunk c.  A group of one
  * needs no reduction: its bias (and GeLU) are applied in the GEMM epilogue
  * and it runs as one launch.  The GEMMs are issued on compute_stream in the

@@ -556,8 +556,8 @@ const char* const kLinearName[4] = {"qkv", "out", "fc1", "fc2"};
 // column sums beside the GEMMs, made the step 3-6% slower); only the
 // reductions, which overlap by design, run beside them.
 //
-// Reductions too short to gain from that stay on cs, between their product
-// and the next: handing one over costs two host calls and a dependency
+// Reductions too short to gain from that stay on cs, behind their products:
+// handing one over costs two host calls and a dependency
 // between two hardware queues, more than a reduction of 8 MB (under 2 us at
 // HBM rate) could hide (h = 512 layer, forward and backward of 256 tokens in 2
 // chunks: 640 us on two streams, 365 so; with 40 MB instead the h = 12288 forward,
@@ -572,6 +572,7 @@ struct Streams {
     bool may_inline = false;   // two streams and no capture
     bool opened = false, cs_joined = false;
     hipEvent_t* ev = nullptr;  // three events: ms before the call, after it, cs after it
+    std::vector<atp::ReduceProblem> late;   // inlined reductions not queued yet
     Streams(void* c, void* m) : cs(static_cast<hipStream_t>(c)), ms(static_cast<hipStream_t>(m)) {}
 
     atp_status begin(hipEvent_t* events) {
@@ -604,7 +605,7 @@ struct Streams {
     }
     // whether chunk reductions of `parts` partials over rows x cols run on cs
     bool inlined(int64_t rows, int64_t cols, int parts, bool b16) const {
-        return may_inline &&
+        return may_inline && parts > 1 &&
                (double)rows * (double)cols * (parts * (b16 ? 2.0 : 4.0) + 2.0) <= kInlineBytes;
     }
     // whether there are reductions and all of them run on cs
@@ -617,27 +618,38 @@ struct Streams {
         }
         return any;
     }
-    // The stream of a reduction whose product was just queued on st (cs, when
-    // the reduction is inlined): ordered after it; `done` marks the product.
-    atp_status reduction(bool inl, hipStream_t st, hipEvent_t done, hipStream_t* rs) {
-        *rs = cs;
-        if (ms == cs) return ATP_OK;
+    // A reduction whose product was just queued on st; `done` marks the
+    // product.  On ms it is queued at once.  An inlined one waits for the next
+    // flush(), so that the products before it run ahead of whatever ms held
+    // before the call, as they do when the reductions run on ms.
+    atp_status reduce(const atp::ReduceProblem& r, bool inl, hipStream_t st, hipEvent_t done) {
         if (inl) {
-            if (!cs_joined) {
-                HIP_CHECK(hipEventRecord(ev[0], ms), "hipEventRecord");
-                HIP_CHECK(hipStreamWaitEvent(cs, ev[0], 0), "hipStreamWaitEvent");
-                cs_joined = true;
-            }
+            late.push_back(r);
             return ATP_OK;
         }
-        HIP_CHECK(hipEventRecord(done, st), "hipEventRecord");
-        HIP_CHECK(hipStreamWaitEvent(ms, done, 0), "hipStreamWaitEvent");
-        *rs = ms;
+        if (ms != cs) {
+            HIP_CHECK(hipEventRecord(done, st), "hipEventRecord");
+            HIP_CHECK(hipStreamWaitEvent(ms, done, 0), "hipStreamWaitEvent");
+        }
+        return run_reduce(r, ms);
+    }
+    // Queues the inlined reductions so far on cs, after ms's earlier work:
+    // before the first launch that reads their results, and at the end.
+    atp_status flush() {
+        if (late.empty()) return ATP_OK;
+        if (!cs_joined) {
+            HIP_CHECK(hipEventRecord(ev[0], ms), "hipEventRecord");
+            HIP_CHECK(hipStreamWaitEvent(cs, ev[0], 0), "hipStreamWaitEvent");
+            cs_joined = true;
+        }
+        for (const atp::ReduceProblem& r : late) ATP_CHECK(run_reduce(r, cs));
+        late.clear();
         return ATP_OK;
     }
     // cs is ordered after all of the block's (and earlier) work on ms, and ms
     // after the reductions on cs
-    atp_status end() const {
+    atp_status end() {
+        ATP_CHECK(flush());
         if (opened) {
             HIP_CHECK(hipEventRecord(ev[1], ms), "hipEventRecord");
             HIP_CHECK(hipStreamWaitEvent(cs, ev[1], 0), "hipStreamWaitEvent");
@@ -1163,7 +1175,7 @@ atp_status weight_grads(const atp_shard& g, bool kn, const void* X, int64_t ldx,
 // with its epilogue in one launch), and the group's partials of those rows are
 // reduced with the epilogue as soon as they are written.  `*done` is recorded
 // after the last chunk's reduction when that runs on ms, else set to NULL (the
-// output is ordered on cs).  make(A_rows, C_rows, ldc, b16, epi, M) builds the product;
+// output is ordered on cs, inlined reductions with the next flush).  make(A_rows, C_rows, ldc, b16, epi, M) builds the product;
 // with a slab, a chunk product with too few tiles is split over k there.
 template <class Make>
 atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* parts,
@@ -1186,11 +1198,9 @@ atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* 
         atp::GemmProblem p = make(static_cast<const uint16_t*>(A) + r0 * lda,
                                   row_ptr(own, r0, ldp, pb16), ldp, pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
-        hipStream_t rs = nullptr;
-        ATP_CHECK(S.reduction(inl, S.cs, ev_chunk[c], &rs));
-        atp::ReduceProblem r = reduce_problem(red_size, parts, ldp, r0, mc, ncols, epi, bias,
-                                              pre_in, out, ldo, true, nullptr, pb16);
-        ATP_CHECK(run_reduce(r, rs));
+        ATP_CHECK(S.reduce(reduce_problem(red_size, parts, ldp, r0, mc, ncols, epi, bias, pre_in,
+                                          out, ldo, true, nullptr, pb16),
+                           inl, S.cs, ev_chunk[c]));
     }
     if (inl || S.ms == S.cs) {
         *done = nullptr;
@@ -1414,7 +1424,8 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
 
     // fc2 reads H: wait for fc1's reduced chunk c (the comm stream runs in
     // order, so chunk chunks-1 means all of H); on the compute stream fc1's
-    // single launch or reductions are ordered before fc2 already
+    // single launch is ordered before fc2 already, its inlined reductions by
+    // the flush
     auto wait_h = [&](int c, hipStream_t st) -> atp_status {
         if (fc1_reduced) HIP_CHECK(hipStreamWaitEvent(st, ev_red1[c], 0), "hipStreamWaitEvent");
         return ATP_OK;
@@ -1440,14 +1451,12 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                          lda_in[L], row_ptr(own, r0, io->ldp[L], pb16),
                                          io->ldp[L], pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, st, two));
-        hipStream_t rs = nullptr;
-        ATP_CHECK(S.reduction(inl[L], st, ev_gemm[L * chunks + c], &rs));
-        atp::ReduceProblem r = reduce_problem(
-            g.red_size, io->partials[L], io->ldp[L], r0, mc, g.n_loc,
-            L == 2 ? atp::EPI_BIAS_GELU : atp::EPI_BIAS, w->b[L], nullptr, outp[L], ldo[L], true,
-            L == 2 ? io->pre : nullptr, pb16);
-        ATP_CHECK(run_reduce(r, rs));
-        if (L == 2 && fc1_reduced) HIP_CHECK(hipEventRecord(ev_red1[c], rs), "hipEventRecord");
+        ATP_CHECK(S.reduce(
+            reduce_problem(g.red_size, io->partials[L], io->ldp[L], r0, mc, g.n_loc,
+                           L == 2 ? atp::EPI_BIAS_GELU : atp::EPI_BIAS, w->b[L], nullptr, outp[L],
+                           ldo[L], true, L == 2 ? io->pre : nullptr, pb16),
+            inl[L], st, ev_gemm[L * chunks + c]));
+        if (L == 2 && fc1_reduced) HIP_CHECK(hipEventRecord(ev_red1[c], S.ms), "hipEventRecord");
         return ATP_OK;
     };
     // Odd chunks go to the second lane unless the chunk products split over
@@ -1457,6 +1466,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     // output, the W^T copy).
     auto linear = [&](int L) -> atp_status {
         const atp_shard& g = P.g[L];
+        if (L == 3 && inl[2]) ATP_CHECK(S.flush());
         if (g.red_size == 1) return unchunked(L);
         ATP_CHECK(need_wt(L));
         int64_t ks = 0;
@@ -1590,7 +1600,8 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
 
     // fc1's dY is dh_pre: wait for fc2's reduced chunk c (chunk chunks-1
     // means all of it, the comm stream runs in order); on the compute stream
-    // fc2's single dX launch or reductions are ordered before fc1 already
+    // fc2's single dX launch is ordered before fc1 already, its inlined
+    // reductions by the flush
     auto wait_dpre = [&](int c) -> atp_status {
         if (fc2_reduced) HIP_CHECK(hipStreamWaitEvent(S.cs, ev_red2[c], 0), "hipStreamWaitEvent");
         return ATP_OK;
@@ -1638,17 +1649,16 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                         ld_dy[L], row_ptr(own, r0, io->ld_dxp[L], pb16),
                                         io->ld_dxp[L], pb16, atp::EPI_NONE, mc);
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
-        hipStream_t rs = nullptr;
-        ATP_CHECK(S.reduction(inl[L], S.cs, ev_gemm[L * chunks + c], &rs));
-        atp::ReduceProblem r = reduce_problem(
-            g.bwd_size, io->dx_partials[L], io->ld_dxp[L], r0, mc, g.k_loc,
-            L == 3 ? atp::EPI_GELU_BWD : atp::EPI_NONE, nullptr, L == 3 ? io->pre : nullptr,
-            dXo[L], ld_dxo[L], true, nullptr, pb16);
-        ATP_CHECK(run_reduce(r, rs));
-        if (L == 3 && fc2_reduced) HIP_CHECK(hipEventRecord(ev_red2[c], rs), "hipEventRecord");
+        ATP_CHECK(S.reduce(
+            reduce_problem(g.bwd_size, io->dx_partials[L], io->ld_dxp[L], r0, mc, g.k_loc,
+                           L == 3 ? atp::EPI_GELU_BWD : atp::EPI_NONE, nullptr,
+                           L == 3 ? io->pre : nullptr, dXo[L], ld_dxo[L], true, nullptr, pb16),
+            inl[L], S.cs, ev_gemm[L * chunks + c]));
+        if (L == 3 && fc2_reduced) HIP_CHECK(hipEventRecord(ev_red2[c], S.ms), "hipEventRecord");
         return ATP_OK;
     };
     auto dx = [&](int L) -> atp_status {
+        if (L == 2 && inl[3]) ATP_CHECK(S.flush());
         if (P.g[L].bwd_size == 1) return dx_unchunked(L);
         for (int c = 0; c < chunks; ++c) ATP_CHECK(dx_chunk(L, c));
         return ATP_OK;
@@ -1783,6 +1793,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
                              io->qkv, io->ld_qkv, T, chunks, ev + 6, &qkv_done, make(0), slab));
     // a causal sequence spans chunks: the core waits for the whole QKV block
     if (qkv_done) HIP_CHECK(hipStreamWaitEvent(S.cs, qkv_done, 0), "hipStreamWaitEvent");
+    ATP_CHECK(S.flush());
     if (T > 0) {
         atp::AttentionProblem p;
         p.qkv = io->qkv;
@@ -1908,6 +1919,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     ATP_CHECK(dweights(go, 1, io->attn, io->ld_attn, io->d_o, io->ld_do, xt_a, dyt_o, S.cs));
     // the core's backward reads the device's columns of the whole d_attn
     if (da_done) HIP_CHECK(hipStreamWaitEvent(S.cs, da_done, 0), "hipStreamWaitEvent");
+    ATP_CHECK(S.flush());
     if (T > 0) {
         atp::AttentionBwdProblem p;
         p.qkv = io->qkv;

@@ -14,6 +14,7 @@ backward) with chunk-based overlapping (Sec. 4.1).
   independent in every step) and, for dW, on sampled columns.
 """
 import itertools
+import time
 
 import numpy as np
 import pytest
@@ -468,3 +469,42 @@ def test_call_orders_both_streams(mesh, bwd):
         seen[1:2].copy_(flags[1:2])
     torch.cuda.synchronize()
     assert seen.tolist() == [1.0, 1.0]
+
+
+@pytest.mark.parametrize("bwd", [False, True], ids=["fwd", "bwd"])
+def test_products_run_ahead_of_a_backlog_on_the_comm_stream(bwd):
+    """Products that need no reduced result do not wait for work queued on
+    comm_stream before the call, also where their reductions run on
+    compute_stream behind it: their partials are there while that work runs."""
+    print(f"comm backlog bwd={bwd}", flush=True)
+    inp = make_block_inputs("col", (2, 2), (1, 0), 256, 512, 0.02, seed=73, on_device=True,
+                            bwd=True)
+    run = run_block_bwd if bwd else run_block_fwd
+    big = torch.empty(128 << 20, device=DEV)
+    comm, probes = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(6)]
+    want = run(inp, 2, comm=comm)
+    torch.cuda.synchronize()
+    backlog = torch.cuda.Event()
+    with torch.cuda.stream(comm):
+        for _ in range(2000):
+            big.fill_(1.0)                  # 512 MB each: some 200 ms together
+        backlog.record()
+    out = run(inp, 2, comm=comm)
+    time.sleep(0.03)                        # the products take some 100 us
+    free = [0, 1] if bwd else [0, 1, 2]     # QKV, out-proj (and fc1): no reduced operand
+    seen = []
+    for st in probes:                       # one that shares comm's hardware queue comes later
+        with torch.cuda.stream(st):
+            vals = [out["own"][i].clone() for i in free]
+            ev = torch.cuda.Event()
+            ev.record()
+        seen.append((ev, vals))
+    time.sleep(0.03)
+    ready = [vals for ev, vals in seen if ev.query()]
+    running = not backlog.query()
+    torch.cuda.synchronize()
+    assert running and ready, (running, len(ready))
+    for i, v in zip(free, ready[0]):
+        assert torch.equal(v, want["own"][i]), i
+    for k in ("dh_pre", "dx_qkv", "dx_fc1", "d_attn") if bwd else ("qkv", "o", "h", "z"):
+        assert torch.equal(_bits(out[k]), _bits(want[k])), k
