@@ -420,15 +420,17 @@ bool fwd_may_copy_w(const BlockPlan& P, int L, int64_t tokens) {
 // copying it costs (4 us and its bytes read and written at 3.5 TB/s).  Split
 // products run from W^T, and so do all in a captured call that do not fill 256 x
 // 256 tiles: the launches of the direct path are not captured (see
-// refuse_capture_of_direct_path).
-bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks, bool capturing) {
+// refuse_capture_of_direct_path).  So do those of a weight whose leading
+// dimension the products do not take.
+bool fwd_reads_w(const BlockPlan& P, int L, int64_t tokens, int chunks, bool capturing,
+                 int64_t ldw) {
     if (!fwd_may_copy_w(P, L, tokens)) return true;
     const atp_shard& g = P.g[L];
     const bool one = g.red_size <= 1;
     const int64_t m = one ? tokens : tokens / chunks;
     int64_t ks = 0;
     if (!one && atp::nt_split_plan(m, g.n_loc, g.k_loc, &ks) > 1) return false;
-    if (capturing) return atp::nn_large_tiles(m, g.n_loc);
+    if (capturing || !atp::gemm_ld_fits(ldw)) return atp::nn_large_tiles(m, g.n_loc);
     const double copy = 4.0 + 4.0 * (double)g.k_loc * (double)g.n_loc / 3.5e6;
     return (one ? 1 : chunks) * atp::nn_extra_us(m, g.n_loc, g.k_loc) < copy;
 }
@@ -1239,8 +1241,11 @@ atp_status weight_grads_ws(const atp_shard& g, bool kn, const void* X, int64_t l
 // forward and backward 993 -> 978).  The wide layer's dW (256 x 256 tiles, 16%
 // slower TN) run from copies.  Both give the same bits.  A captured call always
 // takes the copies: the launches of the direct path are not captured (see
-// refuse_capture_of_direct_path).
-bool dw_direct(const atp_shard& g, bool kn, int64_t T, bool copy_x, bool db) {
+// refuse_capture_of_direct_path); so does one with a leading dimension that
+// the products do not take.
+bool dw_direct(const atp_shard& g, bool kn, int64_t T, int64_t ldx, int64_t lddy, bool copy_x,
+               bool db) {
+    if (!atp::gemm_ld_fits(ldx) || !atp::gemm_ld_fits(lddy)) return false;
     const int64_t M = kn ? g.k_loc : g.n_loc, N = kn ? g.n_loc : g.k_loc;
     auto copy = [&](int64_t cols) { return 3.5 + 4.0 * (double)T * (double)cols / 4.8e6; };
     const double tn = atp::gemm_model_us(atp::LAYOUT_TN, M, N, T) +
@@ -1379,7 +1384,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
             for (int L = 0; L < 4; ++L)
                 if (fwd_may_copy_w(P, L, tokens)) {
                     uint16_t* t = c.take((size_t)P.g[L].n_loc * ws_pitch(P.g[L].k_loc) * 2);
-                    if (!fwd_reads_w(P, L, tokens, chunks, S.capturing)) wt[L] = t;
+                    if (!fwd_reads_w(P, L, tokens, chunks, S.capturing, w->ldw[L])) wt[L] = t;
                 }
         slab = reinterpret_cast<float*>(c.take(slab_bytes(P, tokens, false)));
     }
@@ -1671,7 +1676,8 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         if (L == 2) ATP_CHECK(wait_dpre(chunks - 1));
         const int xi = xsrc[L];
         if (!ws || (!S.capturing &&
-                    dw_direct(g, kn, tokens, !xt_done[xi], io->db[L] != nullptr)))
+                    dw_direct(g, kn, tokens, ldx_in[L], ld_dy[L], !xt_done[xi],
+                              io->db[L] != nullptr)))
             return weight_grads(g, kn, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L], w->ldw[L],
                                 io->db[L], tokens, S.cs);
         // X^T once per source (x serves QKV and fc1), dY^T, then the NT
@@ -1767,7 +1773,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
             for (int L = 0; L < 2; ++L)
                 if (fwd_may_copy_w(P, L, T)) {
                     uint16_t* t = c.take((size_t)P.g[L].n_loc * ws_pitch(P.g[L].k_loc) * 2);
-                    if (!fwd_reads_w(P, L, T, chunks, S.capturing)) wt[L] = t;
+                    if (!fwd_reads_w(P, L, T, chunks, S.capturing, w->ldw[L])) wt[L] = t;
                 }
         slab = reinterpret_cast<float*>(c.take(slab_bytes(P, T, false, 2)));
     }
@@ -1890,7 +1896,8 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     Streams S(compute_stream, comm_stream);
     auto dweights = [&](const atp_shard& g, int L, const void* X, int64_t ldx, const void* dY,
                         int64_t lddy, uint16_t* xt, uint16_t* dyt, hipStream_t s) {
-        if (ws && (S.capturing || !dw_direct(g, kn, T, true, io->db[L] != nullptr)))
+        if (ws &&
+            (S.capturing || !dw_direct(g, kn, T, ldx, lddy, true, io->db[L] != nullptr)))
             return weight_grads_ws(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T,
                                    xt, dyt, colpart, s);
         return weight_grads(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T, s);

@@ -1094,6 +1094,8 @@ const char* gemm_kernel_name(const GemmProblem& p) {
     return p.splits > 1 ? split[l] : names[l][pick_tile(p)];
 }
 
+bool gemm_ld_fits(int64_t ld) { return rows_fit(256, ld); }
+
 double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K) {
     double us = 0.0;
     pick_tile(layout, M, N, K, 1, false, &us);
@@ -1146,7 +1148,7 @@ hipError_t launch_gemm(const GemmProblem& p, hipStream_t s) {
     // buffer offsets are 32-bit: one tile's rows of either operand must span
     // < 2 GiB (256 rows covers every tile but the 320-wide one and the 64 k
     // rows of a row-contiguous operand; pick_tile checks the 320 rows itself)
-    if (!rows_fit(256, p.lda) || !rows_fit(256, p.ldb)) return hipErrorInvalidValue;
+    if (!gemm_ld_fits(p.lda) || !gemm_ld_fits(p.ldb)) return hipErrorInvalidValue;
     const bool b16 = p.out_bf16;
     if (p.nparts > kMaxFusedParts || (p.nparts > 1 && (p.splits > 1 || p.own < 0 ||
                                                        p.own >= p.nparts || p.ldp % 4)))

@@ -66,6 +66,9 @@ double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K);
 // (NN) instead of along k (NT): none on 256 x 256 tiles, about a tenth on the
 // smaller ones (1003 x 2056 x 1608 and 2048 x 6144 x 1024 measured).
 double nn_extra_us(int64_t M, int64_t N, int64_t K);
+// True when launch_gemm takes an operand of leading dimension ld (32-bit
+// offsets span a tile's 256 rows).
+bool gemm_ld_fits(int64_t ld);
 // True when an unsplit NN product [M, N] fills 256 x 256 tiles at least as well
 // as 256 x 160 ones: the workspace keeps no W^T copy for it.
 bool nn_large_tiles(int64_t M, int64_t N);

@@ -118,3 +118,26 @@ def test_benchmark_workload_workspace_equals_direct():
     for i in range(4):
         assert torch.equal(bits(ba["dw"][i]), bits(bb["dw"][i])), f"dw {i}"
         assert torch.equal(bits(ba["db"][i]), bits(bb["db"][i])), f"db {i}"
+
+
+def test_largest_leading_dimension_runs_from_copies():
+    """Leading dimensions of 4M elements are accepted, and more than a product's
+    32-bit offsets span: with a workspace W and X of that pitch are read only
+    by the copies (forward W^T, backward X^T), with the same results."""
+    print("leading dimension 4M", flush=True)
+    T, h = 8, 64
+    inp = make_block_inputs("col", (1, 1), (0, 0), T, h, 0.02, seed=47, bwd=True)
+
+    def wide(t):
+        w = torch.empty((t.shape[0], 1 << 22), dtype=t.dtype, device=t.device)[:, :t.shape[1]]
+        return w.copy_(t)
+    ref, rbwd = run_block_fwd(inp, 1, workspace=True), run_block_bwd(inp, 1, workspace=True)
+    torch.cuda.synchronize()
+    out = run_block_fwd(dict(inp, w=[wide(inp["w"][0])] + inp["w"][1:]), 1, workspace=True)
+    bwd = run_block_bwd(dict(inp, x=wide(inp["x"])), 1, workspace=True)
+    torch.cuda.synchronize()
+    for k in ("qkv", "o", "h", "pre", "z"):
+        assert torch.equal(out[k], ref[k]), k
+    for i in range(4):
+        assert torch.equal(bwd["dw"][i], rbwd["dw"][i]) and torch.equal(bwd["db"][i],
+                                                                        rbwd["db"][i]), i
