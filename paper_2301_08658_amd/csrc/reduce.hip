@@ -148,13 +148,18 @@ hipError_t launch_r(const ReduceProblem& p, hipStream_t s) {
 // loads in flight), a round of CS_T / CL / 8 row blocks at a time.  Through
 // LDS every thread then forms the S_b of one (row block, column) and the first
 // 8 CL threads fold the round's S_b into their columns' sums in ascending b.
-// HBM-bound where the groups fill the chip; a row lane per 64-row block (64
-// loads in sequence) left three quarters of the lanes idle at 2048 rows
-// (2048 x 4096: 25.6 us, one lane per group and 16-column blocks 6.2).
-// CL = 8 reads 128-byte row segments; with fewer than 128 such blocks, CL = 2
-// quadruples the blocks (neighbours, on one XCD, share the lines in its L2).
+// The next round's rows are on their way while a round is folded.
+// Bound by the rows in flight: 8192 x 6144 25.6 us (3.9 TB/s; 39.9 with 16
+// columns a block and no row ahead), 2048 x 4096 7 (25.6 with one row lane per
+// 64-row block, 64 loads in sequence, which took 30.4 for 8192 x 6144).
 // Blocks are renumbered so neighbouring column groups run on the same XCD.
 constexpr int CS_T = 1024;               // threads per block
+
+// A workgroup barrier over LDS accesses only: __syncthreads() would also wait
+// for the loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
 
 template <int CL>
 __global__ __launch_bounds__(CS_T) void colsum_kernel(const uint16_t* __restrict__ dy, int64_t ld,
@@ -174,17 +179,21 @@ __global__ __launch_bounds__(CS_T) void colsum_kernel(const uint16_t* __restrict
     const int64_t nb = (T + 63) / 64;
     const int sb = threadIdx.x / COLS, sc = threadIdx.x % COLS;
     float acc = 0.0f;                      // column blk * COLS + threadIdx.x (first COLS threads)
+    u32x4 w[8];                            // this lane's rows of the round
+    auto load = [&](int64_t r0) {
+        if (c < N && r0 < T) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                w[i] = *reinterpret_cast<const u32x4*>(dy + min(r0 + i, T - 1) * ld + c);
+        }
+    };
+    load((int64_t)ty * 8);
     for (int64_t b0 = 0; b0 < nb; b0 += RB) {
         const int64_t r0 = b0 * 64 + ty * 8;
         float gs[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) gs[e] = 0.0f;
-        if (c < N && r0 < T) {
-            u32x4 w[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-                w[i] = r0 + i < T ? *reinterpret_cast<const u32x4*>(dy + (r0 + i) * ld + c)
-                                  : u32x4{0, 0, 0, 0};
+        if (c < N) {
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (r0 + i < T) {
@@ -194,9 +203,10 @@ __global__ __launch_bounds__(CS_T) void colsum_kernel(const uint16_t* __restrict
                     for (int e = 0; e < 8; ++e) gs[e] += f[e];
                 }
         }
+        load(r0 + RB * 64);                // in flight while this round is folded
 #pragma unroll
         for (int e = 0; e < 8; ++e) gsum[ty][tx * 8 + e] = gs[e];
-        __syncthreads();
+        lds_barrier();
         // the groups of row block b0 + sb inside [0, T)
         const int64_t left = T - (b0 + sb) * 64;
         const int ng = left <= 0 ? 0 : left >= 64 ? 8 : (int)((left + 7) / 8);
@@ -205,7 +215,7 @@ __global__ __launch_bounds__(CS_T) void colsum_kernel(const uint16_t* __restrict
         for (int g = 0; g < 8; ++g)
             if (g < ng) s += gsum[sb * 8 + g][sc];
         bsum[sb][sc] = s;
-        __syncthreads();
+        lds_barrier();
         if (threadIdx.x < COLS) {
             const int nr = nb - b0 < RB ? (int)(nb - b0) : RB;
 #pragma unroll 8
@@ -298,13 +308,19 @@ hipError_t launch_colsum(const void* dy, int64_t ld, int64_t T, int64_t N, float
                          hipStream_t s) {
     if (N <= 0) return hipSuccess;
     const uint16_t* y = static_cast<const uint16_t*>(dy);
-    const int64_t wide = (N + 63) / 64;
-    if (wide >= 128)
-        hipLaunchKernelGGL((colsum_kernel<8>), dim3((unsigned)wide), dim3(CS_T), 0, s, y, ld, T, N,
-                           db);
-    else
-        hipLaunchKernelGGL((colsum_kernel<2>), dim3((unsigned)((N + 15) / 16)), dim3(CS_T), 0, s, y,
-                           ld, T, N, db);
+    // Column lanes: 2 while one block per CU covers the columns (its 32-byte row
+    // segments cost more than they give in a second round), else the one of 4 and
+    // 8 with the least work in its rounds of 256 blocks; few rows don't pay the
+    // launch of more than 256 blocks.  8192 rows (us for 2, 4, 8): 3072 columns 20
+    // 23 27, 6144 34 26 29, 10240 39 46 34, 20480 89 71 86; 64 rows of 20480: 9 7 6.
+    auto rounds = [&](int w) { return (N + 256 * 8 * w - 1) / (256 * 8 * w) * w; };
+    const int cl = N <= 256 * 16                                           ? 2
+                   : rounds(4) < rounds(8) && (N <= 256 * 32 || T >= 1000) ? 4
+                                                                           : 8;
+    const dim3 blocks((unsigned)((N + 8 * cl - 1) / (8 * cl)));
+    if (cl == 8) hipLaunchKernelGGL((colsum_kernel<8>), blocks, dim3(CS_T), 0, s, y, ld, T, N, db);
+    else if (cl == 4) hipLaunchKernelGGL((colsum_kernel<4>), blocks, dim3(CS_T), 0, s, y, ld, T, N, db);
+    else hipLaunchKernelGGL((colsum_kernel<2>), blocks, dim3(CS_T), 0, s, y, ld, T, N, db);
     return hipGetLastError();
 }
 

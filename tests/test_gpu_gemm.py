@@ -167,11 +167,13 @@ def test_every_tile_and_layout_integer_bit_exact(tile, M, N, K):
         assert torch.equal(out.double(), ref), lay
 
 
-@pytest.mark.parametrize("T,N", [(1, 8), (4099, 40), (130, 72), (5000, 8200), (1024, 8192)])
+@pytest.mark.parametrize("T,N", [(1, 8), (4099, 40), (130, 72), (2100, 4096), (2100, 4104),
+                                 (1024, 8192), (5000, 8200), (3, 16392), (1030, 16392)])
 def test_bias_gradient_rounds_and_widths_integer_bit_exact(T, N):
     """db alone (the column sum) over one and several rounds of row blocks,
-    in 16-column blocks and, from 128 of them on, 64-column blocks, with
-    partial 8-row groups, row blocks and column blocks."""
+    in blocks of 16, 32 and 64 columns (up to 4096 columns; up to 8192 and,
+    from 1000 rows on, past 16384; the others), with partial 8-row groups, row
+    blocks and column blocks."""
     print(f"column sum {T}x{N}", flush=True)
     dy = S.randint_bf16((T, N), 9, 1).to(DEV)
     x, w = S.randint_bf16((T, 8), 9, 2).to(DEV), S.randint_bf16((8, N), 9, 3).to(DEV)
