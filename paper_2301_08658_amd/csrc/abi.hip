@@ -1236,9 +1236,12 @@ atp_status weight_grads_ws(const atp_shard& g, bool kn, const void* X, int64_t l
 // True when dW of a linear reads X and dY as given (TN, db by the column sum)
 // although the workspace has places for X^T and dY^T: the TN product's extra
 // time is less than the copies'.  Modelled: the products by their tiles, a
-// copy 3.5 us and its bytes at 4.8 TB/s (8192 x 6144 41 us), the column sum 4 us
-// and dY at 5 TB/s (h = 4096 layer backward 1577 -> 1561 us, attention block
-// forward and backward 993 -> 978).  The wide layer's dW (256 x 256 tiles, 16%
+// copy 5 us and its bytes at 6 TB/s (8192 x 6144 37 us), the column sum 6 us and
+// 1.2 us per 1000 rows or 5 us and dY at 5.5 TB/s (8192 x 6144 25 us).  Of 40
+// linears of 256 to 8192 tokens (h = 512 to 20480) timed both ways it takes the
+// faster for all but 8192 x 4096 x 8192 (467 us as given, 489 from copies) and
+// 8192 x 8192 x 4096 (462, 471); 2048 x 3072 x 6144 takes 107 and 103 us, 8192 x
+// 1024 x 6144 133 and 174.  The wide layer's dW (256 x 256 tiles, 16%
 // slower TN) run from copies.  Both give the same bits.  A captured call always
 // takes the copies: the launches of the direct path are not captured (see
 // refuse_capture_of_direct_path); so does one with a leading dimension that
@@ -1247,9 +1250,10 @@ bool dw_direct(const atp_shard& g, bool kn, int64_t T, int64_t ldx, int64_t lddy
                bool db) {
     if (!atp::gemm_ld_fits(ldx) || !atp::gemm_ld_fits(lddy)) return false;
     const int64_t M = kn ? g.k_loc : g.n_loc, N = kn ? g.n_loc : g.k_loc;
-    auto copy = [&](int64_t cols) { return 3.5 + 4.0 * (double)T * (double)cols / 4.8e6; };
-    const double tn = atp::gemm_model_us(atp::LAYOUT_TN, M, N, T) +
-                      (db ? 4.0 + 2.0 * (double)T * (double)g.n_loc / 5e6 : 0.0);
+    auto copy = [&](int64_t cols) { return 5.0 + 4.0 * (double)T * (double)cols / 6e6; };
+    const double colsum = std::max(6.0 + 1.2e-3 * (double)T,
+                                   5.0 + 2.0 * (double)T * (double)g.n_loc / 5.5e6);
+    const double tn = atp::gemm_model_us(atp::LAYOUT_TN, M, N, T) + (db ? colsum : 0.0);
     const double nt = atp::gemm_model_us(atp::LAYOUT_NT, M, N, T) + copy(g.n_loc) +
                       (copy_x ? copy(g.k_loc) : 0.0) + (db ? 3.0 : 0.0);
     return tn < nt;

@@ -1098,7 +1098,7 @@ bool gemm_ld_fits(int64_t ld) { return rows_fit(256, ld); }
 
 double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K) {
     double us = 0.0;
-    pick_tile(layout, M, N, K, 1, false, &us);
+    pick_tile(layout, M, N, K, 1, true, &us);
     return us;
 }
 
