@@ -191,12 +191,15 @@ def test_chunk_count_never_changes_a_bit(workspace):
             assert torch.equal(out[key], base[key]), (chunks, key)
 
 
+@pytest.mark.parametrize("T", [512, 2048])
 @pytest.mark.parametrize("mode,mesh,coord", [("row", (4, 2), (3, 1)), ("col", (8, 1), (5, 0)),
                                              ("col", (1, 4), (0, 2))])
-def test_serialized_equals_pipelined(mode, mesh, coord):
+def test_serialized_equals_pipelined(mode, mesh, coord, T):
     """One stream, and compute + comm streams, give the same bits (groups of
-    one and of several members)."""
-    inp = make_block_inputs(mode, mesh, coord, 512, 1024, 0.02, seed=5, bwd=True)
+    one and of several members).  At 512 tokens all chunk reductions move at
+    most 8 MB and stay on the compute stream; at 2048 the large ones run on the
+    comm stream, beside chunk products on two lanes."""
+    inp = make_block_inputs(mode, mesh, coord, T, 1024, 0.02, seed=5, bwd=True)
     runs = [dict(same_stream=True), dict()]
     fw = [run_block_fwd(inp, 4, **kw) for kw in runs]
     torch.cuda.synchronize()
@@ -369,12 +372,14 @@ def test_bf16_partials(case, workspace):
             assert torch.equal(_bits(one[key]), _bits(out[key])), key
 
 
-def test_concurrent_calls_from_two_threads():
+@pytest.mark.parametrize("T", [512, 2048])
+def test_concurrent_calls_from_two_threads(T):
     """Two host threads run block calls on their own streams at the same
-    time.  Each thread keeps its own synchronisation events, so every call
+    time.  Each thread keeps its own synchronisation events and second lane
+    (used at 2048 tokens, with reductions on the comm stream), so every call
     gives the bits of the same call made alone."""
     import threading
-    cases = [make_block_inputs("col", (2, 4), (1, 2), 512, 1024, 0.02, seed=71 + i)
+    cases = [make_block_inputs("col", (2, 4), (1, 2), T, 1024, 0.02, seed=71 + i)
              for i in range(2)]
     ref = [run_block_fwd(c, 4) for c in cases]
     torch.cuda.synchronize()
@@ -403,14 +408,16 @@ def test_concurrent_calls_from_two_threads():
                 assert torch.equal(_bits(out[key]), _bits(ref[i][key])), (i, key)
 
 
-@pytest.mark.parametrize("T,h,chunks", [(256, 512, 2), (130, 512, 1), (4096, 2048, 2)])
-def test_reductions_keep_their_place_on_the_comm_stream(T, h, chunks):
+@pytest.mark.parametrize("mesh,T,h,chunks", [((2, 2), 256, 512, 2), ((2, 2), 130, 512, 1),
+                                             ((2, 2), 4096, 2048, 2), ((2, 4), 2048, 1024, 2)])
+def test_reductions_keep_their_place_on_the_comm_stream(mesh, T, h, chunks):
     """Peers' partials written on comm_stream just before the call are in the
     sums, and work queued there after the call finds the outputs written,
     whether the reductions ran on comm_stream (the large case) or, being
-    short, on compute_stream."""
-    print(f"comm stream order T={T} h={h}", flush=True)
-    inp = make_block_inputs("col", (2, 2), (1, 0), T, h, 0.02, seed=71, on_device=True, bwd=True)
+    short, on compute_stream, or some on each (2 x 4: forward QKV and fc1, and
+    backward out-proj and fc2, on comm_stream)."""
+    print(f"comm stream order {mesh} T={T} h={h}", flush=True)
+    inp = make_block_inputs("col", mesh, (1, 0), T, h, 0.02, seed=71, on_device=True, bwd=True)
     ref = run_block_fwd(inp, chunks, same_stream=True)
     rbwd = run_block_bwd(inp, chunks, same_stream=True)
     torch.cuda.synchronize()

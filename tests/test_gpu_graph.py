@@ -222,10 +222,11 @@ def _attention_block_call(case, seed, workspace, keep=None):
 
 
 ATTN_CASES = [("col", (2, 4), (1, 2), 2048, 16, 2, 256, 2),   # forward chunk products split
-              ("col", (8, 1), (3, 0), 2048, 16, 1, 512, 4)]
+              ("col", (8, 1), (3, 0), 2048, 16, 1, 512, 4),
+              ("col", (2, 4), (1, 2), 1024, 8, 1, 200, 2)]    # a partial block of 64 tokens
 
 
-@pytest.mark.parametrize("case", ATTN_CASES, ids=lambda c: f"{c[0]}{c[1][0]}x{c[1][1]}")
+@pytest.mark.parametrize("case", ATTN_CASES, ids=lambda c: f"{c[0]}{c[1][0]}x{c[1][1]}_h{c[3]}")
 def test_attention_block_graph_replay_equals_eager(case):
     """The chained attention block (forward, then backward) on its workspace
     path captured as a HIP graph: three replays, with eager fills and an

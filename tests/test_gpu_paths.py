@@ -3,7 +3,9 @@ the same calls without one.
 
 With a workspace the forward runs from W^T and dW from X^T and dY^T (both
 operands contiguous along k); without one they read W, X and dY as given
-(transposing LDS reads).  Both layouts sum each element's products in the
+(transposing LDS reads), and so does a call with one where its model has the
+copies cost more than they give: every dW of the small cases here, so the
+copies have cases of their own.  Both layouts sum each element's products in the
 same order, so the paths give the same bits, except that with a workspace
 chunk products with too few output tiles to fill the chip are split over k,
 which sums in a different order: there the paths agree to fp32 rounding,
@@ -98,6 +100,44 @@ def _check_bwd_paths(a, b):
         rel = 2e-3 if i == 2 else 1e-4
         assert_paths_agree(a["dw"][i], b["dw"][i], f"dw {i}", rel)
         assert_paths_agree(a["db"][i], b["db"][i], f"db {i}", rel)
+
+
+def _names(fn):
+    atp.atp_profile_enable(1)
+    try:
+        fn()
+        torch.cuda.synchronize()
+        return {r["name"]: r["launches"] for r in atp.atp_profile_collect(256)}
+    finally:
+        atp.atp_profile_enable(0)
+
+
+# sizes at which all four dW run from copies: long token ranges of few columns,
+# whose last 64-row block of column partials holds 8 rows
+COPY_CASES = [("col", (4, 2), (1, 0), 8200, 512, 2), ("row", (1, 8), (0, 5), 8200, 512, 1)]
+
+
+@pytest.mark.parametrize("layout", [atp.ATP_W_KN, atp.ATP_W_NK], ids=["kn", "nk"])
+@pytest.mark.parametrize("case", COPY_CASES, ids=lambda c: f"{c[0]}{c[1][0]}x{c[1][1]}")
+def test_weight_gradients_from_copies_equal_direct(case, layout):
+    """dW and db from X^T (one copy of x for QKV and fc1) and dY^T against the
+    call that reads X and dY as given: the profile shows which ran."""
+    mode, mesh, coord, T, h, chunks = case
+    print(f"dW copies {case} layout {layout}", flush=True)
+    inp = make_block_inputs(mode, mesh, coord, T, h, 0.02, seed=24, on_device=True, bwd=True,
+                            layout=layout)
+    res = []
+    a = _names(lambda: res.append(run_block_bwd(inp, chunks)))
+    b = _names(lambda: res.append(run_block_bwd(inp, chunks, workspace=True)))
+    assert any(n.startswith("gemm_tn") for n in a) and "transpose" not in a, a
+    assert not any(n.startswith("gemm_tn") for n in b), b
+    # X^T of x, attention block and H, dY^T of four linears, and with weights
+    # stored [n][k] their four [k][n] copies
+    assert b["transpose"] == (7 if layout == atp.ATP_W_KN else 11), b
+    _check_bwd_paths(*res)
+    for i in (0, 1, 3):     # fc1's dY is a reduced product, which may be split
+        assert torch.equal(bits(res[0]["dw"][i]), bits(res[1]["dw"][i])), f"dw {i}"
+        assert torch.equal(bits(res[0]["db"][i]), bits(res[1]["db"][i])), f"db {i}"
 
 
 def test_benchmark_workload_workspace_equals_direct():
