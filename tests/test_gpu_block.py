@@ -478,6 +478,27 @@ def test_call_orders_both_streams(mesh, bwd):
     assert seen.tolist() == [1.0, 1.0]
 
 
+def _stream_of_another_queue(big):
+    """A stream whose work does not hold back the current stream's: streams
+    share a few hardware queues, and one of the same queue runs in order."""
+    small = torch.empty(1024, device=DEV)
+    for _ in range(16):
+        st, busy, free = torch.cuda.Stream(), torch.cuda.Event(), torch.cuda.Event()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(st):
+            for _ in range(200):
+                big.fill_(1.0)              # some 20 ms together
+            busy.record()
+        small.fill_(1.0)
+        free.record()
+        time.sleep(0.005)
+        found = free.query() and not busy.query()
+        torch.cuda.synchronize()
+        if found:
+            return st
+    raise AssertionError("every stream shares the current stream's queue")
+
+
 @pytest.mark.parametrize("bwd", [False, True], ids=["fwd", "bwd"])
 def test_products_run_ahead_of_a_backlog_on_the_comm_stream(bwd):
     """Products that need no reduced result do not wait for work queued on
@@ -488,7 +509,7 @@ def test_products_run_ahead_of_a_backlog_on_the_comm_stream(bwd):
                             bwd=True)
     run = run_block_bwd if bwd else run_block_fwd
     big = torch.empty(128 << 20, device=DEV)
-    comm, probes = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(6)]
+    comm, probes = _stream_of_another_queue(big), [torch.cuda.Stream() for _ in range(6)]
     want = run(inp, 2, comm=comm)
     torch.cuda.synchronize()
     backlog = torch.cuda.Event()
