@@ -500,21 +500,15 @@ __global__ __launch_bounds__(nt::NT, 1) void gemm_nt_kernel(KArgs a) {
                 const uint16_t* sa = ringA + (p % RA) * A_EL;
                 const uint16_t* sb = ringB + (p % RB) * B_EL;
                 const bool ahead = p + 2 < nk;
-                // The fragments of both k-contiguous operands are read before the
-                // copies are issued: they arrive while the wave stands at the
-                // copies (4096 x 10240 x 20480: 1332 -> 1296 us, 4096^3 107 -> 104).
-                // The transposing reads of a row-contiguous B are the other way
-                // round (512 x 20480 x 10240: 220 us, reads first 243).
-                constexpr bool READ_FIRST = A_K && B_K;
-                auto copies = [&]() {
-                    if (!grpB) {
-                        if (p + 1 < nk)
-                            cb.issue(ringB + ((p + 1) % RB) * B_EL, (int64_t)(p + 1) * BK, w4);
-                    } else if (ahead) {
-                        ca.issue(ringA + ((p + 2) % RA) * A_EL, (int64_t)(p + 2) * BK, w4);
-                    }
-                };
-                if constexpr (!READ_FIRST) copies();
+                // The copies are issued before the fragments are read.  The other order
+                // was 1-2% faster at 4096^3 and 2% slower on average over 40 NT shapes
+                // (841 x 11672 x 8960 208 us, reads first 232; 2226 x 5504 x 4608 105, 113),
+                // and 10% slower with B along its rows (512 x 20480 x 10240 220, 243).
+                if (!grpB) {
+                    if (p + 1 < nk) cb.issue(ringB + ((p + 1) % RB) * B_EL, (int64_t)(p + 1) * BK, w4);
+                } else if (ahead) {
+                    ca.issue(ringA + ((p + 2) % RA) * A_EL, (int64_t)(p + 2) * BK, w4);
+                }
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
@@ -523,10 +517,6 @@ __global__ __launch_bounds__(nt::NT, 1) void gemm_nt_kernel(KArgs a) {
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
                         fb[ks][j] = op_frag<BN, B_K, BK>(sb, wn * WN + j * MF, ks, lane);
-                }
-                if constexpr (READ_FIRST) {
-                    __builtin_amdgcn_sched_barrier(0);
-                    copies();
                 }
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 // group B: its copies of step p+1 have landed (those of p+2 may fly)
