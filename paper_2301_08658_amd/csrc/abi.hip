@@ -833,6 +833,7 @@ atp_status atp_shard_linear_fwd(const atp_mesh* mesh, int32_t mode, int64_t toke
             static_cast<char*>(y) + r0 * ldy * esz, ldy, b16, epi, (c - c0 + 1) * mc, g.n_loc,
             g.k_loc);
         p.bias = bias_loc;
+        p.alone = !chunk_done;   // events are there for reductions beside the next chunks
         if (preact) p.pre_out = static_cast<uint16_t*>(preact) + r0 * ldy;
         ATP_CHECK(run_gemm(p, s));
         if (chunk_done && chunk_done[c])
@@ -946,6 +947,7 @@ atp_status atp_shard_linear_fwd_fused(const atp_mesh* mesh, int32_t mode, int64_
                                       out_dtype == ATP_BF16, epi, tokens, g.n_loc, g.k_loc);
     p.bias = bias_loc;
     p.pre_out = preact;
+    p.alone = true;
     if (g.red_size > 1) {
         p.nparts = g.red_size;
         p.own = g.red_index;
@@ -979,6 +981,7 @@ atp_status atp_shard_linear_bwd(const atp_mesh* mesh, int32_t mode, int64_t toke
                                           static_cast<const uint16_t*>(dy) + r0 * lddy, lddy,
                                           w_loc, ldw, dx_partial + r0 * lddx, lddx, false,
                                           atp::EPI_NONE, (c - c0 + 1) * mc, g.k_loc, g.n_loc);
+        p.alone = !dx_chunk_done;
         ATP_CHECK(run_gemm(p, s));
         if (dx_chunk_done && dx_chunk_done[c])
             HIP_CHECK(hipEventRecord(static_cast<hipEvent_t>(dx_chunk_done[c]), s),
@@ -987,6 +990,7 @@ atp_status atp_shard_linear_bwd(const atp_mesh* mesh, int32_t mode, int64_t toke
     // dW = X^T dY over all tokens
     atp::GemmProblem p = gemm_problem(atp::LAYOUT_TN, x_loc, ldx, dy, lddy, dw, lddw, false,
                                       atp::EPI_NONE, g.k_loc, g.n_loc, tokens);
+    p.alone = !dx_chunk_done;
     ATP_CHECK(run_gemm(p, s));
     if (db) ATP_CHECK(run_colsum(dy, lddy, tokens, g.n_loc, db, s));
     return ATP_OK;

@@ -892,30 +892,55 @@ bool rows_fit(int64_t rows, int64_t ld) { return rows * ld * 2 <= kMaxSpan; }
 // [146], 256 x 64 103 [109]; 256 x 128: 64 x 128 98 [97], 192 x 128 104 [110], 512 x
 // 64 123 [127]; 128 x 128: 64 x 64 28 [31], 192 x 192 106 [100], 1024 x 64 145 [161];
 // 64 x 128: 256 x 128 49 [50], 128 x 64 22 [21]; 64 x 64: 256 x 64 18 [18], 1024 x
-// 64 64 [62].  256 x 160 is charged more than alone (256 x 320 368 [408]): it
-// leaves no CU to a reduction beside it (4096 x 2560 x 20480 in the wide layer's
-// step: 727 us, 435 on 160 tiles of 256 x 256).  For the same reason a smaller
-// tile has to beat the 256 x 256 ones by 5%.
+// 64 64 [62].  None has an epilogue term (GeLU adds 5 us to a launch of 28).  NN has
+// its own row for 256 x 128 (13382 x 1600 x 9240: 506 us on 256 x 256, 588 on 256 x
+// 128, which the NT row put ahead).
+//
+// 256 x 160 leaves no CU to a reduction beside it (4096 x 2560 x 20480 in the wide
+// layer's step: 727 us, 435 on 160 tiles of 256 x 256), so where reductions may run
+// beside the product it is charged more than it takes (256 x 320 368 [408]) and
+// serves NT only.  Products with nothing beside them (alone) have it, and 256 x 320,
+// at their own rates, fitted to 750 log-uniform shapes in each layout with every tile
+// timed: there 256 x 160 is the fastest tile of 8% (NN), 6% (NT) and 5% (TN), by up to
+// 24% over the next (9159 x 960 x 8024 NN 204 us, 230 on 256 x 256; 1004 x 8952 x 9496
+// NT 262, 313; 17872 x 440 x 904 TN 38, 44).  On 350 other shapes the picks lose 0.4%
+// (NN), 0.5% and 0.5% to the best tile on average; charged as beside reductions they
+// lost 1.1-1.4%.  A smaller tile has to beat the 256 x 256 ones by 5% for the same
+// reason, and alone because the fit is no closer.
 enum TileCfg { T_256, T_160, T_320, T_256x128, T_128, T_64x128, T_64, T_COUNT };
 
 struct TileCost { int bm, bn, percu; double t1, tf, o0, ox; };
-// k-contiguous A (NT, and NN, whose 160-wide tiles are slower)
+// k-contiguous A
 constexpr TileCost kCostNT[T_COUNT] = {
     {256, 256, 1, 1.10, 1.55, 4.0, 6.0}, {256, 160, 1, 1.00, 1.25, 3.0, 5.0},
     {256, 320, 1, 1.50, 2.35, 4.0, 7.0}, {256, 128, 1, 0.72, 0.88, 3.0, 4.0},
     {128, 128, 1, 0.42, 0.56, 3.0, 1.5}, {64, 128, 1, 0.29, 0.36, 2.5, 1.2},
     {64, 64, 2, 0.235, 0.42, 2.5, 0.7}};
-constexpr double kNN160 = 1.2;
 // both operands along their rows (TN)
 constexpr TileCost kCostTN[T_COUNT] = {
-    {256, 256, 1, 1.50, 1.80, 4.0, 6.0}, {256, 160, 1, 1.62, 1.75, 3.0, 5.0},
+    {256, 256, 1, 1.50, 1.80, 4.0, 6.0}, {256, 160, 1, 0, 0, 0, 0},
     {256, 320, 1, 0, 0, 0, 0},           {256, 128, 1, 0.82, 1.00, 3.0, 4.0},
     {128, 128, 1, 0.48, 0.62, 3.0, 1.5}, {64, 128, 1, 0.34, 0.42, 2.5, 1.2},
     {64, 64, 2, 0.26, 0.46, 2.5, 0.7}};
+constexpr TileCost kNN256x128 = {256, 128, 1, 0.64, 1.02, 3.0, 3.1};
+// alone
+constexpr TileCost kAlone160NN = {256, 160, 1, 0.89, 1.09, 3.0, 4.9};
+constexpr TileCost kAlone160NT = {256, 160, 1, 0.96, 1.13, 3.0, 4.1};
+constexpr TileCost kAlone160TN = {256, 160, 1, 1.46, 1.52, 3.0, 3.7};
+constexpr TileCost kAlone320 = {256, 320, 1, 1.32, 2.28, 4.0, 7.4};
 
-double tile_cost(int layout, TileCfg c, int64_t M, int64_t N, int64_t K, int S) {
+const TileCost& tile_row(int layout, TileCfg c, bool alone) {
+    if (layout == LAYOUT_NN && c == T_256x128) return kNN256x128;
+    if (alone && c == T_160)
+        return layout == LAYOUT_NN ? kAlone160NN : layout == LAYOUT_NT ? kAlone160NT : kAlone160TN;
+    if (alone && c == T_320) return kAlone320;
+    return layout == LAYOUT_TN ? kCostTN[c] : kCostNT[c];
+}
+
+double tile_cost(int layout, TileCfg c, int64_t M, int64_t N, int64_t K, int S,
+                 bool alone = false) {
     constexpr int64_t kCUs = 256;
-    const TileCost t = layout == LAYOUT_TN ? kCostTN[c] : kCostNT[c];
+    const TileCost& t = tile_row(layout, c, alone);
     const int64_t tiles = ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * S;
     const double steps = (double)((K + 63) / 64);
     const int64_t round = kCUs * t.percu, full = tiles / round, rest = tiles % round;
@@ -925,17 +950,18 @@ double tile_cost(int layout, TileCfg c, int64_t M, int64_t N, int64_t K, int S) 
         const double step = t.percu == 1 ? t.t1 + (t.tf - t.t1) * x * x : x > 1.0 ? t.tf : t.t1;
         us += step * steps + t.o0 + t.ox * x;
     }
-    return layout == LAYOUT_NN && c == T_160 ? us * kNN160 : us;
+    return us;
 }
 
 TileCfg pick_tile(int layout, int64_t M, int64_t N, int64_t K, int S, bool allow320,
-                  double* us = nullptr) {
+                  double* us = nullptr, bool alone = false) {
     TileCfg best = T_256;
     double least = tile_cost(layout, T_256, M, N, K, S);
     for (int i = T_160; i < T_COUNT; ++i) {
         const TileCfg c = (TileCfg)i;
+        if (c == T_160 && layout != LAYOUT_NT && !alone) continue;
         if (c == T_320 && !(allow320 && layout == LAYOUT_NT && S == 1)) continue;
-        const double u = tile_cost(layout, c, M, N, K, S);
+        const double u = tile_cost(layout, c, M, N, K, S, alone);
         if (u < (best == T_256 ? 0.95 : 1.0) * least) {
             best = c;
             least = u;
@@ -963,7 +989,8 @@ TileCfg pick_seg_tile(int64_t M, int64_t N, int64_t K, double* us = nullptr) {
 TileCfg pick_tile(const GemmProblem& p) {
     if (p.seg > 0) return pick_seg_tile(p.M, p.N, p.K);
     return pick_tile(p.layout, p.M, p.N, p.splits > 1 ? p.ksplit : p.K,
-                     p.splits > 1 ? p.splits : 1, rows_fit(320, p.ldb));
+                     p.splits > 1 ? p.splits : 1, rows_fit(320, p.ldb), nullptr,
+                     p.alone && p.splits <= 1);
 }
 
 // Split-K plan of an NT product written to fp32: the S in 1..kMaxSplits
@@ -1095,7 +1122,7 @@ double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K) {
 double nn_extra_us(int64_t M, int64_t N, int64_t K) {
     double us = 0.0;
     const TileCfg c = pick_tile(LAYOUT_NN, M, N, K, 1, false, &us);
-    return c == T_256 ? 0.0 : c == T_160 ? us - us / kNN160 : 0.1 * us;
+    return c == T_256 ? 0.0 : 0.1 * us;
 }
 
 bool nn_large_tiles(int64_t M, int64_t N) {

@@ -35,6 +35,8 @@ struct GemmProblem {
     // NT, EPI_NONE, no split: > 0 sums segments of seg k (a multiple of 64)
     // one after the other in the tile, the bits of that split's slab sum
     int64_t seg = 0;
+    // no reduction runs beside the product (the choice of tile; no effect on the bits)
+    bool alone = false;
     // fused peer sum (NN, no split): when nparts > 1 the epilogue forms
     // sum_{j < nparts} P_j in group order before bias / GeLU, with P_own the
     // tile's own accumulators and the others read from peers[j] (fp32, ld ldp)
@@ -60,7 +62,8 @@ int nt_split_plan(int64_t M, int64_t N, int64_t K, int64_t* ksplit);
 // True when a product with a split plan forms its sums in one launch (seg)
 // rather than in slabs; lanes: its chunks may run on two streams then.
 bool nt_plan_in_tile(int64_t M, int64_t N, int64_t K, bool lanes);
-// Modelled time (us) of an unsplit product on the tiles it would take.
+// Modelled time (us) of an unsplit product on the tiles it would take beside
+// reductions.
 double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K);
 // Modelled time (us) that an unsplit product loses by reading B along its rows
 // (NN) instead of along k (NT): none on 256 x 256 tiles, about a tenth on the
@@ -70,7 +73,8 @@ double nn_extra_us(int64_t M, int64_t N, int64_t K);
 // offsets span a tile's 256 rows).
 bool gemm_ld_fits(int64_t ld);
 // True when an unsplit NN product [M, N] fills 256 x 256 tiles at least as well
-// as 256 x 160 ones: the workspace keeps no W^T copy for it.
+// as 256 x 160 ones (NT): the workspace keeps no W^T copy for it.  The line fixes
+// the workspace's size, so it does not follow the tile model.
 bool nn_large_tiles(int64_t M, int64_t N);
 
 constexpr int kMaxParts = 64;

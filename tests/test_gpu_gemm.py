@@ -54,7 +54,7 @@ def test_bwd_nt_tn_colsum_integer_bit_exact(T, K, N, chunks):
                                           (257, 168, 40, 1), (700, 488, 1000, 2),
                                           (512, 160, 2056, 4), (1024, 1288, 72, 8)])
 def test_dx_nt_ragged_integer_bit_exact(T, K, N, chunks):
-    """dX = dY W^T runs the NT kernel (256 x 160 tiles, K steps of 64):
+    """dX = dY W^T on the small tiles (64 x 64 to 128 x 128):
     outputs of one row, sub-tile and multi-tile sizes with ragged edges, and
     contractions shorter than one K step or ending in a partial one."""
     m = atp.mesh(1, 1)
@@ -132,10 +132,11 @@ def test_fwd_leading_dimensions_and_empty():
 @pytest.mark.parametrize("tile,M,N,K", [
     ("64", 8, 8, 8), ("64", 520, 1160, 72), ("64x128", 1000, 1032, 136), ("128", 520, 6152, 200),
     ("128", 1000, 2056, 1608), ("256x128", 1000, 6152, 136), ("256x128", 776, 6152, 1000),
-    ("256", 2048, 8000, 328)])
+    ("256", 2048, 8000, 328), ("256", 1400, 7160, 1000), ("256", 520, 13608, 40),
+    ("", 4872, 1544, 40), ("", 520, 10904, 328), ("", 520, 13088, 1608)])
 def test_every_tile_and_layout_integer_bit_exact(tile, M, N, K):
-    """Each tile configuration in the three layouts (NN forward, NT dX, TN
-    dW) at sizes with partial tiles on both sides and a partial last K step
+    """Each tile configuration that serves the three layouts (NN forward, NT
+    dX, TN dW; no suffix: 256 x 160) at sizes with partial tiles on both sides and a partial last K step
     (one shorter than the copy ring), against the 64-bit product: integer
     inputs keep every fp32 sum exact.  The profile names the tile that ran."""
     m = atp.mesh(1, 1)
@@ -165,6 +166,30 @@ def test_every_tile_and_layout_integer_bit_exact(tile, M, N, K):
         assert any(n.startswith(f"gemm_{lay}{tile}_") for n in names), (lay, names)
         ref = torch.matmul(a.double(), b.double())
         assert torch.equal(out.double(), ref), lay
+
+
+@pytest.mark.parametrize("tile,M,N,K", [
+    ("320", 1310, 10800, 72), ("320", 1537, 9240, 40), ("320", 1537, 9240, 1000),
+    ("256", 533, 13608, 360), ("", 4867, 1544, 72)])
+def test_large_k_contiguous_tiles_ragged_integer_bit_exact(tile, M, N, K):
+    """256 x 320 (K steps of 32), 256 x 256 and 256 x 160 of a product with both
+    operands along k (dX): rows that are no multiple of 8, partial last row and
+    column tiles, a contraction of one or two K steps and a partial last one,
+    against the 64-bit product of integer inputs."""
+    m = atp.mesh(1, 1)
+    print(f"NT tile {tile or 160} {M}x{N}x{K}", flush=True)
+    dy, w = S.randint_bf16((M, K), 11, 1).to(DEV), S.randint_bf16((N, K), 11, 2).to(DEV)
+    x, dw = S.randint_bf16((M, N), 11, 3).to(DEV), torch.empty((N, K), device=DEV)
+    dx = torch.full((M, N), float("nan"), device=DEV)
+    atp.atp_profile_enable(1)
+    try:
+        atp.atp_shard_linear_bwd(m, 0, M, N, K, 1, x, w, dy, dx, dw)
+        _sync()
+        names = [r["name"] for r in atp.atp_profile_collect(8)]
+    finally:
+        atp.atp_profile_enable(0)
+    assert f"gemm_nt{tile}_e0_f32" in names, names
+    assert torch.equal(dx.double(), torch.matmul(dy.double(), w.double().t()))
 
 
 @pytest.mark.parametrize("T,N", [(1, 8), (4099, 40), (130, 72), (2100, 4096), (2100, 4104),
