@@ -1095,20 +1095,19 @@ bool gemm_supported(int layout, int epi, bool out_bf16) {
 
 const char* gemm_kernel_name(const GemmProblem& p) {
     static const char* const names[3][T_COUNT] = {
-        {"gemm_nn256", "gemm_nn", "gemm_nn320", "gemm_nn256x128", "gemm_nn128", "gemm_nn64x128",
-         "gemm_nn64"},
+        {"gemm_nn256", "gemm_nn", "", "gemm_nn256x128", "gemm_nn128", "gemm_nn64x128", "gemm_nn64"},
         {"gemm_nt256", "gemm_nt", "gemm_nt320", "gemm_nt256x128", "gemm_nt128", "gemm_nt64x128",
          "gemm_nt64"},
-        {"gemm_tn256", "gemm_tn", "gemm_tn320", "gemm_tn256x128", "gemm_tn128", "gemm_tn64x128",
-         "gemm_tn64"}};
-    static const char* const split[3] = {"gemm_nn_splitk", "gemm_nt_splitk", "gemm_tn_splitk"};
+        {"gemm_tn256", "gemm_tn", "", "gemm_tn256x128", "gemm_tn128", "gemm_tn64x128", "gemm_tn64"}};
+    static const char* const split[T_COUNT] = {
+        "gemm_nt_splitk_256", "gemm_nt_splitk", "", "gemm_nt_splitk_256x128", "gemm_nt_splitk_128",
+        "gemm_nt_splitk_64x128", "gemm_nt_splitk_64"};
     const int l = p.layout == LAYOUT_NN ? 0 : p.layout == LAYOUT_NT ? 1 : p.layout == LAYOUT_TN ? 2 : -1;
     if (l < 0) return "gemm_?";
-    if (p.seg > 0) {
-        const TileCfg c = pick_tile(p);
+    const TileCfg c = pick_tile(p);
+    if (p.seg > 0)
         return c == T_128 ? "gemm_nt_seg128" : c == T_64x128 ? "gemm_nt_seg64x128" : "gemm_nt_seg64";
-    }
-    return p.splits > 1 ? split[l] : names[l][pick_tile(p)];
+    return p.splits > 1 ? split[c] : names[l][c];
 }
 
 bool gemm_ld_fits(int64_t ld) { return rows_fit(256, ld); }

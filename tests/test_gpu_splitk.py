@@ -3,7 +3,8 @@
 A chunk's product with too few 256 x 160 tiles to fill the chip is split over
 its contraction: each split writes an fp32 slab, and the slabs are summed in
 split order into the device's own partial buffer before the chunk's
-reduction reads it.  The split plan is a function of the chunk's shape.
+reduction reads it, or the tile adds the splits' sums itself.  The split plan
+is a function of the chunk's shape.
 
 * the split kernels run where the plan asks for them (the library's profile),
 * results match the oracle, with odd split counts and a shorter last split,
@@ -134,7 +135,9 @@ def split_plan(M, N, K):
 
 
 # (mesh, tokens, h, chunks, same stream, partials, names of split products):
-# slabs and every tile that sums the segments itself, on one and two lanes
+# slabs and every tile that sums the segments itself, on one and two lanes, then
+# slabs from every tile that writes them (splitk_e0: 256 x 160), the last split
+# shorter than the others
 ORDER_CASES = [
     ((2, 2), 512, 4096, 1, True, torch.float32, ("seg128", "seg64")),
     ((2, 2), 1024, 4096, 2, False, torch.bfloat16, ("seg128",)),
@@ -142,6 +145,12 @@ ORDER_CASES = [
     ((2, 2), 1000, 2000, 1, True, torch.float32, ("seg64",)),
     ((4, 2), 1600, 2048, 2, False, torch.bfloat16, ("seg64x128",)),
     ((2, 2), 200, 2000, 1, True, torch.bfloat16, ("splitk",)),
+    ((2, 2), 8, 1600, 1, True, torch.float32, ("splitk_64",)),
+    ((2, 2), 80, 1600, 1, True, torch.float32, ("splitk_64x128",)),
+    ((2, 2), 200, 1600, 1, True, torch.float32, ("splitk_128",)),
+    ((2, 2), 272, 1600, 1, True, torch.float32, ("splitk_256x128",)),
+    ((2, 2), 720, 3200, 1, True, torch.float32, ("splitk_256",)),
+    ((2, 4), 1240, 3200, 1, True, torch.float32, ("splitk_e0",)),
 ]
 
 
@@ -159,12 +168,12 @@ def test_own_partials_are_the_plans_splits_summed_in_order(mesh, T, h, chunks, s
     for kind in kinds:
         assert any(n.startswith(f"gemm_nt_{kind}_") for n in names), (kind, names)
     one, some = atp.mesh(1, 1), False
-    for i, g in enumerate(inp["G"][:3]):
+    for i, g in enumerate(inp["G"]):
         if g.red_size == 1:
             continue
         S, ks = split_plan(T // chunks, g.n_loc, g.k_loc)
         some |= S > 1
-        xin, want = (inp["a"] if i == 1 else inp["x"]), None
+        xin, want = (inp["x"], inp["a"], inp["x"], out["h"])[i], None
         for k0 in range(0, g.k_loc, ks):
             k1 = min(k0 + ks, g.k_loc)
             y = torch.empty((T, g.n_loc), device=xin.device)
