@@ -192,6 +192,47 @@ def test_large_k_contiguous_tiles_ragged_integer_bit_exact(tile, M, N, K):
     assert torch.equal(dx.double(), torch.matmul(dy.double(), w.double().t()))
 
 
+@pytest.mark.parametrize("epi", [atp.ATP_EPI_NONE, atp.ATP_EPI_BIAS, atp.ATP_EPI_BIAS_GELU])
+def test_tiles_of_calls_with_and_without_events_same_bits(epi):
+    """A forward runs on 256 x 160 tiles where nothing is beside it and on others
+    where the caller passes chunk events, with the same bits; so do the fused
+    peer sum there and the product with its reduction."""
+    T, K, N = 520, 328, 10904
+    print(f"alone and with events epi={epi}", flush=True)
+    x, w = S.randn_bf16((T, K), 1.0, 12, 1).to(DEV), S.randn_bf16((K, N), 0.05, 12, 2).to(DEV)
+    b = S.randn_bf16((N,), 0.5, 12, 3).to(DEV) if epi != atp.ATP_EPI_NONE else None
+    out, pre, names = [], [], []
+    for ev in (None, [atp.HipEvent()]):
+        y = torch.full((T, N), float("nan"), device=DEV, dtype=torch.bfloat16)
+        q = torch.empty_like(y) if epi == atp.ATP_EPI_BIAS_GELU else None
+        atp.atp_profile_enable(1)
+        try:
+            atp.atp_shard_linear_fwd(atp.mesh(1, 1), 0, T, K, N, 1, x, w, b, epi, y, preact=q,
+                                     chunk_done=ev)
+            _sync()
+            names.append([r["name"] for r in atp.atp_profile_collect(8)][0])
+        finally:
+            atp.atp_profile_enable(0)
+        out.append(y)
+        pre.append(q)
+    assert names[0].startswith("gemm_nn_e") and not names[1].startswith("gemm_nn_e"), names
+    assert torch.equal(*out) and (pre[0] is None or torch.equal(*pre))
+    # a group of two: the fused peer sum on 256 x 160 against product, then reduction
+    m = atp.mesh(2, 1, 1, 0)
+    g = atp.atp_shard_geometry(m, atp.ATP_ROW_FIRST, 2 * K, N)
+    assert (g.k_loc, g.n_loc, g.red_size, g.red_index) == (K, N, 2, 1)
+    peer, own = S.randn_f32((T, N), 1.0, 12, 4).to(DEV), torch.empty((T, N), device=DEV)
+    atp.atp_shard_linear_fwd(m, atp.ATP_ROW_FIRST, T, 2 * K, N, 1, x, w, None, atp.ATP_EPI_NONE, own)
+    want, fused = torch.empty_like(out[0]), torch.empty_like(out[0])
+    pw, pf = ((torch.empty_like(want), torch.empty_like(want))
+              if epi == atp.ATP_EPI_BIAS_GELU else (None, None))
+    atp.atp_chunked_partial_reduce(2, T, N, 1, [peer, own], b, epi, want, preact_out=pw)
+    atp.atp_shard_linear_fwd_fused(m, atp.ATP_ROW_FIRST, T, 2 * K, N, x, w, [peer, None], b, epi,
+                                   fused, pf)
+    _sync()
+    assert torch.equal(want, fused) and (pw is None or torch.equal(pw, pf))
+
+
 @pytest.mark.parametrize("T,N", [(1, 8), (4099, 40), (130, 72), (2100, 4096), (2100, 4104),
                                  (1024, 8192), (5000, 8200), (3, 16392), (1030, 16392)])
 def test_bias_gradient_rounds_and_widths_integer_bit_exact(T, N):
