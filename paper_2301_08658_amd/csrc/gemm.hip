@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "epilogue_math.h"
@@ -990,7 +991,7 @@ TileCfg pick_tile(const GemmProblem& p) {
     if (p.seg > 0) return pick_seg_tile(p.M, p.N, p.K);
     return pick_tile(p.layout, p.M, p.N, p.splits > 1 ? p.ksplit : p.K,
                      p.splits > 1 ? p.splits : 1, rows_fit(320, p.ldb), nullptr,
-                     p.alone && p.splits <= 1);
+                     p.alone || p.splits > 1);
 }
 
 // Split-K plan of an NT product written to fp32: the S in 1..kMaxSplits
@@ -1121,7 +1122,8 @@ double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K) {
 double nn_extra_us(int64_t M, int64_t N, int64_t K) {
     double us = 0.0;
     const TileCfg c = pick_tile(LAYOUT_NN, M, N, K, 1, false, &us);
-    return c == T_256 ? 0.0 : 0.1 * us;
+    const double tiles = us - gemm_model_us(LAYOUT_NT, M, N, K);
+    return std::max(tiles, c == T_256 ? 0.0 : 0.1 * us);
 }
 
 bool nn_large_tiles(int64_t M, int64_t N) {
@@ -1153,7 +1155,7 @@ bool nt_plan_in_tile(int64_t M, int64_t N, int64_t K, bool lanes) {
     if (S <= 1) return false;
     const double el = (double)M * (double)N;
     double slabs = 0.0, tile = 0.0;
-    pick_tile(LAYOUT_NT, M, N, ks, S, false, &slabs);
+    pick_tile(LAYOUT_NT, M, N, ks, S, false, &slabs, true);
     slabs += 4.0 * S * el <= 16e6 ? 4.0 * S * el / 1e7 : 4.0 * (S + 1) * el / 3.3e6;
     pick_seg_tile(lanes ? 2 * M : M, N, K, &tile);
     return lanes ? 0.5 * tile < slabs : tile < 0.9 * slabs;

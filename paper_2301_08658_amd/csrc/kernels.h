@@ -67,7 +67,8 @@ bool nt_plan_in_tile(int64_t M, int64_t N, int64_t K, bool lanes);
 double gemm_model_us(int layout, int64_t M, int64_t N, int64_t K);
 // Modelled time (us) that an unsplit product loses by reading B along its rows
 // (NN) instead of along k (NT): none on 256 x 256 tiles, about a tenth on the
-// smaller ones (1003 x 2056 x 1608 and 2048 x 6144 x 1024 measured).
+// smaller ones (1003 x 2056 x 1608 and 2048 x 6144 x 1024 measured), or what the
+// tiles of NT gain (6920 x 2656 x 21248: 889 us on 256 x 256, 767 NT on 256 x 320).
 double nn_extra_us(int64_t M, int64_t N, int64_t K);
 // True when launch_gemm takes an operand of leading dimension ld (32-bit
 // offsets span a tile's 256 rows).

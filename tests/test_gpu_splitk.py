@@ -149,8 +149,8 @@ ORDER_CASES = [
     ((2, 2), 80, 1600, 1, True, torch.float32, ("splitk_64x128",)),
     ((2, 2), 200, 1600, 1, True, torch.float32, ("splitk_128",)),
     ((2, 2), 272, 1600, 1, True, torch.float32, ("splitk_256x128",)),
-    ((2, 2), 720, 3200, 1, True, torch.float32, ("splitk_256",)),
-    ((2, 4), 1240, 3200, 1, True, torch.float32, ("splitk_e0",)),
+    ((2, 2), 2384, 4000, 1, True, torch.float32, ("splitk_256",)),
+    ((2, 2), 928, 2400, 1, True, torch.float32, ("splitk_e0",)),
 ]
 
 
