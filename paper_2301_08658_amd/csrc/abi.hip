@@ -572,6 +572,7 @@ struct Streams {
     hipStream_t cs, ms;
     bool capturing = false;    // cs is under graph capture
     bool may_inline = false;   // two streams and no capture
+    bool beside = false;       // some reduction runs on ms, beside products
     bool opened = false, cs_joined = false;
     hipEvent_t* ev = nullptr;  // three events: ms before the call, after it, cs after it
     std::vector<atp::ReduceProblem> late;   // inlined reductions not queued yet
@@ -610,15 +611,22 @@ struct Streams {
         return may_inline && parts > 1 &&
                (double)rows * (double)cols * (parts * (b16 ? 2.0 : 4.0) + 2.0) <= kInlineBytes;
     }
-    // whether there are reductions and all of them run on cs
-    static bool all_inlined(const bool* inl, std::initializer_list<int32_t> groups) {
-        bool any = false;
+    // With the groups of the call's linears and which are inlined: whether
+    // some reduction runs on ms, and the opening of ms unless all run on cs.
+    atp_status plan(const bool* inl, std::initializer_list<int32_t> groups, hipEvent_t start) {
+        bool any = false, handed = false;
         for (int32_t g : groups) {
-            if (g > 1 && !*inl) return false;
             any |= g > 1;
+            handed |= g > 1 && !*inl;
             ++inl;
         }
-        return any;
+        beside = handed && ms != cs;
+        return any && !handed ? ATP_OK : open(start);
+    }
+    // A product of the call on st.
+    atp_status gemm(atp::GemmProblem p, hipStream_t st) const {
+        p.alone = !beside;
+        return run_gemm(p, st);
     }
     // A reduction whose product was just queued on st; `done` marks the
     // product.  On ms it is queued at once.  An inlined one waits for the next
@@ -1166,14 +1174,14 @@ atp::GemmProblem dyw_problem(const atp_shard& g, bool kn, const void* W, int64_t
 
 atp_status weight_grads(const atp_shard& g, bool kn, const void* X, int64_t ldx, const void* dY,
                         int64_t lddy, float* dw, int64_t ldw, float* db, int64_t T,
-                        hipStream_t s) {
-    if (db) ATP_CHECK(run_colsum(dY, lddy, T, g.n_loc, db, s));
+                        const Streams& S) {
+    if (db) ATP_CHECK(run_colsum(dY, lddy, T, g.n_loc, db, S.cs));
     atp::GemmProblem p =
         kn ? gemm_problem(atp::LAYOUT_TN, X, ldx, dY, lddy, dw, ldw, false, atp::EPI_NONE, g.k_loc,
                           g.n_loc, T)
            : gemm_problem(atp::LAYOUT_TN, dY, lddy, X, ldx, dw, ldw, false, atp::EPI_NONE, g.n_loc,
                           g.k_loc, T);
-    return run_gemm(p, s);
+    return S.gemm(p, S.cs);
 }
 
 // One reduced product of the chain, chunked (Sec. 4.1): chunk c's GEMM on
@@ -1194,7 +1202,7 @@ atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* 
         p.bias = bias;
         p.pre_in = pre_in;
         *done = nullptr;
-        return run_gemm(p, S.cs);
+        return S.gemm(p, S.cs);
     }
     const int64_t mc = T / chunks;
     const bool inl = S.inlined(mc, ncols, red_size, pb16);
@@ -1203,6 +1211,7 @@ atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* 
         const int64_t r0 = (int64_t)c * mc;
         atp::GemmProblem p = make(static_cast<const uint16_t*>(A) + r0 * lda,
                                   row_ptr(own, r0, ldp, pb16), ldp, pb16, atp::EPI_NONE, mc);
+        p.alone = !S.beside;
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
         ATP_CHECK(S.reduce(reduce_problem(red_size, parts, ldp, r0, mc, ncols, epi, bias, pre_in,
                                           out, ldo, true, nullptr, pb16),
@@ -1223,18 +1232,18 @@ atp_status chained_linear(Streams& S, int red_size, int red_index, void* const* 
 atp_status weight_grads_ws(const atp_shard& g, bool kn, const void* X, int64_t ldx,
                            const void* dY, int64_t lddy, float* dw, int64_t ldw, float* db,
                            int64_t T, uint16_t* xt, uint16_t* dyt, float* colpart,
-                           hipStream_t s) {
+                           const Streams& S) {
     const int64_t tp = ws_pitch(T);
-    ATP_CHECK(run_transpose(X, ldx, T, g.k_loc, xt, tp, s));
+    ATP_CHECK(run_transpose(X, ldx, T, g.k_loc, xt, tp, S.cs));
     float* part = db ? colpart : nullptr;
-    ATP_CHECK(run_transpose(dY, lddy, T, g.n_loc, dyt, tp, s, part, g.n_loc));
-    if (part) ATP_CHECK(run_colsum_finish(part, g.n_loc, (T + 63) / 64, g.n_loc, db, s));
+    ATP_CHECK(run_transpose(dY, lddy, T, g.n_loc, dyt, tp, S.cs, part, g.n_loc));
+    if (part) ATP_CHECK(run_colsum_finish(part, g.n_loc, (T + 63) / 64, g.n_loc, db, S.cs));
     const atp::GemmProblem p =
         kn ? gemm_problem(atp::LAYOUT_NT, xt, tp, dyt, tp, dw, ldw, false, atp::EPI_NONE, g.k_loc,
                           g.n_loc, T)
            : gemm_problem(atp::LAYOUT_NT, dyt, tp, xt, tp, dw, ldw, false, atp::EPI_NONE, g.n_loc,
                           g.k_loc, T);
-    return run_gemm(p, s);
+    return S.gemm(p, S.cs);
 }
 
 // True when dW of a linear reads X and dY as given (TN, db by the column sum)
@@ -1430,8 +1439,8 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     bool inl[4];
     for (int L = 0; L < 4; ++L)
         inl[L] = S.inlined(mc, P.g[L].n_loc, P.g[L].red_size, pb16);
-    if (!S.all_inlined(inl, {P.g[0].red_size, P.g[1].red_size, P.g[2].red_size, P.g[3].red_size}))
-        ATP_CHECK(S.open(ev[5]));
+    ATP_CHECK(S.plan(
+        inl, {P.g[0].red_size, P.g[1].red_size, P.g[2].red_size, P.g[3].red_size}, ev[5]));
     // fc1's H is reduced on ms
     const bool fc1_reduced = P.g[2].red_size > 1 && S.ms != S.cs && !inl[2];
 
@@ -1450,7 +1459,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                          L == 2 ? atp::EPI_BIAS_GELU : atp::EPI_BIAS, tokens);
         p.bias = w->b[L];
         p.pre_out = (L == 2) ? io->pre : nullptr;
-        return run_gemm(p, S.cs);
+        return S.gemm(p, S.cs);
     };
     // chunk c: the GEMM writes this device's partial rows, the comm stream
     // reduces the group's partials for those rows as soon as they are ready
@@ -1463,6 +1472,7 @@ atp_status atp_block_fwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         atp::GemmProblem p = fwd_problem(L, static_cast<const uint16_t*>(A_in[L]) + r0 * lda_in[L],
                                          lda_in[L], row_ptr(own, r0, io->ldp[L], pb16),
                                          io->ldp[L], pb16, atp::EPI_NONE, mc);
+        p.alone = !S.beside;
         ATP_CHECK(run_nt_partial(p, slab, st, two));
         ATP_CHECK(S.reduce(
             reduce_problem(g.red_size, io->partials[L], io->ldp[L], r0, mc, g.n_loc,
@@ -1606,8 +1616,8 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
     bool inl[4];
     for (int L = 0; L < 4; ++L)
         inl[L] = S.inlined(mc, P.g[L].k_loc, P.g[L].bwd_size, pb16);
-    if (!S.all_inlined(inl, {P.g[0].bwd_size, P.g[1].bwd_size, P.g[2].bwd_size, P.g[3].bwd_size}))
-        ATP_CHECK(S.open(ev[3]));
+    ATP_CHECK(S.plan(
+        inl, {P.g[0].bwd_size, P.g[1].bwd_size, P.g[2].bwd_size, P.g[3].bwd_size}, ev[3]));
     // fc2's dX is reduced on ms
     const bool fc2_reduced = P.g[3].bwd_size > 1 && S.ms != S.cs && !inl[3];
 
@@ -1650,7 +1660,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                                         L == 3 ? atp::EPI_GELU_BWD : atp::EPI_NONE, tokens);
         p.pre_in = (L == 3) ? io->pre : nullptr;
         (void)g;
-        return run_gemm(p, S.cs);
+        return S.gemm(p, S.cs);
     };
     auto dx_chunk = [&](int L, int c) -> atp_status {
         const atp_shard& g = P.g[L];
@@ -1661,6 +1671,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
         atp::GemmProblem p = dx_problem(L, static_cast<const uint16_t*>(dY[L]) + r0 * ld_dy[L],
                                         ld_dy[L], row_ptr(own, r0, io->ld_dxp[L], pb16),
                                         io->ld_dxp[L], pb16, atp::EPI_NONE, mc);
+        p.alone = !S.beside;
         ATP_CHECK(run_nt_partial(p, slab, S.cs));
         ATP_CHECK(S.reduce(
             reduce_problem(g.bwd_size, io->dx_partials[L], io->ld_dxp[L], r0, mc, g.k_loc,
@@ -1687,7 +1698,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                     dw_direct(g, kn, tokens, ldx_in[L], ld_dy[L], !xt_done[xi],
                               io->db[L] != nullptr)))
             return weight_grads(g, kn, Xin[L], ldx_in[L], dY[L], ld_dy[L], io->dw[L], w->ldw[L],
-                                io->db[L], tokens, S.cs);
+                                io->db[L], tokens, S);
         // X^T once per source (x serves QKV and fc1), dY^T, then the NT
         // product over the tokens
         const int64_t tp = ws_pitch(tokens);
@@ -1707,7 +1718,7 @@ atp_status atp_block_bwd(const atp_mesh* mesh, int32_t block_mode, int64_t token
                               atp::EPI_NONE, g.k_loc, g.n_loc, tokens)
                : gemm_problem(atp::LAYOUT_NT, dyt[L], tp, xt[xi], tp, io->dw[L], w->ldw[L], false,
                               atp::EPI_NONE, g.n_loc, g.k_loc, tokens);
-        return run_gemm(p, S.cs);
+        return S.gemm(p, S.cs);
     };
     // fc2's dX first (it makes dh_pre, which fc1 waits for); then the
     // attention projections' dX, whose reductions can start at once; then
@@ -1771,7 +1782,7 @@ atp_status atp_attention_block_fwd(const atp_mesh* mesh, int32_t block_mode, int
     hipEvent_t qkv_done = ev[3], o_done = ev[4];
     const bool inl[2] = {S.inlined(T / chunks, gq.n_loc, gq.red_size, pb16),
                          S.inlined(T / chunks, go.n_loc, go.red_size, pb16)};
-    if (!S.all_inlined(inl, {gq.red_size, go.red_size})) ATP_CHECK(S.open(ev[5]));
+    ATP_CHECK(S.plan(inl, {gq.red_size, go.red_size}, ev[5]));
 
     uint16_t* wt[2] = {nullptr, nullptr};
     float* slab = nullptr;
@@ -1903,12 +1914,12 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     }
     Streams S(compute_stream, comm_stream);
     auto dweights = [&](const atp_shard& g, int L, const void* X, int64_t ldx, const void* dY,
-                        int64_t lddy, uint16_t* xt, uint16_t* dyt, hipStream_t s) {
+                        int64_t lddy, uint16_t* xt, uint16_t* dyt) {
         if (ws &&
             (S.capturing || !dw_direct(g, kn, T, ldx, lddy, true, io->db[L] != nullptr)))
             return weight_grads_ws(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T,
-                                   xt, dyt, colpart, s);
-        return weight_grads(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T, s);
+                                   xt, dyt, colpart, S);
+        return weight_grads(g, kn, X, ldx, dY, lddy, io->dw[L], w->ldw[L], io->db[L], T, S);
     };
 
     hipEvent_t* ev = nullptr;
@@ -1919,7 +1930,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
     hipEvent_t da_done = ev[3], dx_done = ev[4];
     const bool inl[2] = {S.inlined(T / chunks, gq.k_loc, gq.bwd_size, pb16),
                          S.inlined(T / chunks, go.k_loc, go.bwd_size, pb16)};
-    if (!S.all_inlined(inl, {gq.bwd_size, go.bwd_size})) ATP_CHECK(S.open(ev[5]));
+    ATP_CHECK(S.plan(inl, {gq.bwd_size, go.bwd_size}, ev[5]));
     auto make = [&](int L, const void* dY, int64_t lddy) {
         return [&, L, lddy](const void* A, void* C, int64_t ldc, bool b16, int epi, int64_t M) {
             return dyw_problem(P.g[L], kn, w->w[L], w->ldw[L], A, lddy, C, ldc, b16, epi, M);
@@ -1931,7 +1942,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
                              io->d_o, io->ld_do, go.k_loc, atp::EPI_NONE, nullptr, nullptr,
                              io->d_attn, io->ld_d_attn, T, chunks, ev + 6, &da_done,
                              make(1, io->d_o, io->ld_do)));
-    ATP_CHECK(dweights(go, 1, io->attn, io->ld_attn, io->d_o, io->ld_do, xt_a, dyt_o, S.cs));
+    ATP_CHECK(dweights(go, 1, io->attn, io->ld_attn, io->d_o, io->ld_do, xt_a, dyt_o));
     // the core's backward reads the device's columns of the whole d_attn
     if (da_done) HIP_CHECK(hipStreamWaitEvent(S.cs, da_done, 0), "hipStreamWaitEvent");
     ATP_CHECK(S.flush());
@@ -1963,7 +1974,7 @@ atp_status atp_attention_block_bwd(const atp_mesh* mesh, int32_t block_mode, int
                              io->d_qkv, io->ld_dqkv, gq.k_loc, atp::EPI_NONE, nullptr, nullptr,
                              io->dx, io->ld_dx, T, chunks, ev + 6 + chunks, &dx_done,
                              make(0, io->d_qkv, io->ld_dqkv)));
-    ATP_CHECK(dweights(gq, 0, io->x_loc, io->ldx, io->d_qkv, io->ld_dqkv, xt_x, dyt_q, S.cs));
+    ATP_CHECK(dweights(gq, 0, io->x_loc, io->ldx, io->d_qkv, io->ld_dqkv, xt_x, dyt_q));
     return S.end();
 }
 

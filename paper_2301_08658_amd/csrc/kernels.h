@@ -35,7 +35,8 @@ struct GemmProblem {
     // NT, EPI_NONE, no split: > 0 sums segments of seg k (a multiple of 64)
     // one after the other in the tile, the bits of that split's slab sum
     int64_t seg = 0;
-    // no reduction runs beside the product (the choice of tile; no effect on the bits)
+    // no reduction of the call runs beside the product (the choice of tile; the
+    // bits are the same)
     bool alone = false;
     // fused peer sum (NN, no split): when nparts > 1 the epilogue forms
     // sum_{j < nparts} P_j in group order before bias / GeLU, with P_own the
