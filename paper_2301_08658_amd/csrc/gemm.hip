@@ -906,8 +906,10 @@ bool rows_fit(int64_t rows, int64_t ld) { return rows * ld * 2 <= kMaxSpan; }
 // 24% over the next (9159 x 960 x 8024 NN 204 us, 230 on 256 x 256; 1004 x 8952 x 9496
 // NT 262, 313; 17872 x 440 x 904 TN 38, 44).  On 350 other shapes the picks lose 0.4%
 // (NN), 0.5% and 0.5% to the best tile on average; charged as beside reductions they
-// lost 1.1-1.4%.  A smaller tile has to beat the 256 x 256 ones by 5% for the same
-// reason, and alone because the fit is no closer.
+// lost 0.9-1.4% on 400 of the first.  Split products, whose tiles fill whole rounds,
+// take the same rates (232 x 19136 x 4784 in splits: 79 us charged, 69).  A smaller
+// tile has to beat the 256 x 256 ones by 5% for the same reason, and alone because
+// the fit is no closer.
 enum TileCfg { T_256, T_160, T_320, T_256x128, T_128, T_64x128, T_64, T_COUNT };
 
 struct TileCost { int bm, bn, percu; double t1, tf, o0, ox; };
